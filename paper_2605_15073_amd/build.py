@@ -11,12 +11,14 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libcgtp.so")
-SOURCES = ["plan.cpp", "tables.cpp", "order.cpp", "contract.hip", "kernels.hip", "onsite.hip", "receiver_mfma.hip", "folded.hip",
+SOURCES = ["plan.cpp", "tables.cpp", "order.cpp", "contract.hip", "kernels.hip", "onsite.hip", "receiver_mfma.hip",
+           "receiver_values.hip", "folded.hip",
            "fourier_mfma.hip", "noalloc.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-# Per-source flags. The receiver's matrix-core results feed vector ALU products at once:
+# Per-source flags. The receivers' matrix-core results feed vector ALU products at once:
 # accumulating them in VGPRs (not AccVGPRs) saves a copy per result element and registers.
-SOURCE_FLAGS = {"receiver_mfma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+SOURCE_FLAGS = {src: ["-mllvm", "-amdgpu-mfma-vgpr-form"]
+                for src in ("receiver_mfma.hip", "receiver_values.hip")}
 
 # Packed fp32 VALU ops are disabled for all device code.
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",

@@ -33,6 +33,9 @@ __device__ __forceinline__ int isqrt_small(int t)
 }
 
 typedef float float4_t __attribute__((ext_vector_type(4)));
+typedef float float2_t __attribute__((ext_vector_type(2)));
+typedef unsigned uint2_t __attribute__((ext_vector_type(2)));
+typedef __bf16 bf2_t __attribute__((ext_vector_type(2)));
 
 // Raw buffer resource over [base, base + bytes): loads past the end return 0.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void *base, unsigned bytes)
@@ -218,11 +221,17 @@ constexpr int kSB = 34;          // LDS row stride of a staged X row (kCk * kLG 
 constexpr int kSW = kTile + 16;  // LDS row stride of Ws: lane groups of a half-wave apart
 constexpr int kNX = kTile * kCk * kLG / kThreadsC;  // staged elements per thread and slice
 
+// PARTS: the output as bf16 triples in the slot vectors of the values-only receiver,
+// Yp [B][rtiles][3][ndg][16 ranks][8 degrees] (4 up to lmax 3), ranks r0 + o (zeros for o in
+// [Cout, oend)): a lane's kLG = 4 degrees of one rank are half a slot vector (or a whole one of
+// 4), one 8-byte store per part.
+template <bool PARTS>
 __global__ __launch_bounds__(kThreadsC, 4) void k_contract_kdeg(
     int64_t B, int Cin, int Cout, int L, int otiles, int lgroups, const float *__restrict__ W,
     unsigned w_bytes, int w_sl, int w_si, int w_so, const float *__restrict__ X, int x_sb,
     float *__restrict__ Y, int64_t y_sb, int64_t y_so, int64_t y_sk,
-    const float *__restrict__ scale, bool accumulate)
+    const float *__restrict__ scale, bool accumulate, uint2_t *__restrict__ Yp, int rtiles, int r0,
+    int oend)
 {
     __shared__ float Xs[kTile * kSB];
     __shared__ float Ws[kLG][kCk][kSW];
@@ -238,7 +247,7 @@ __global__ __launch_bounds__(kThreadsC, 4) void k_contract_kdeg(
     const int64_t b0 = grp * kTile;
     const int o0 = ot * kTile;
     const int l0 = lg * kLG;
-    const int nl = (L - l0 < kLG) ? (L - l0) : kLG;
+    const int nl = (L - l0 < kLG) ? (L - l0) : kLG;  // PARTS: <= 0 for degrees past lmax (zeros)
     const int nb = (B - b0 < kTile) ? (int)(B - b0) : kTile;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -283,6 +292,7 @@ __global__ __launch_bounds__(kThreadsC, 4) void k_contract_kdeg(
             wr[s2] = bload(ws, wo4);
         }
     };
+    if (PARTS && nl <= 0) Cin = 0;
     fetch(0);
     for (int i0 = 0; i0 < Cin; i0 += kCk) {
         __syncthreads();  // the previous slice is consumed
@@ -308,6 +318,40 @@ __global__ __launch_bounds__(kThreadsC, 4) void k_contract_kdeg(
             }
     }
     // D[b = 4 g + j][o = n] of each 16 x 16 tile
+    if constexpr (PARTS) {
+        float sc[kLG];
+#pragma unroll
+        for (int l = 0; l < kLG; ++l) sc[l] = l < nl ? scale[l0 + l] : 0.f;
+        const int ndg = rt_groups(L - 1), vw = rt_vec_bytes(L - 1) / 8;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const int o = o0 + wo + 16 * c + n, r = r0 + o;
+            if (o >= oend) continue;
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int b = wb + 16 * a + 4 * g + j;
+                    if (b >= nb) continue;
+                    uint2_t *y = Yp + (((b0 + b) * rtiles + (r >> 4)) * 3 * ndg + l0 / kRtPart) * 16 * vw +
+                                 (r & 15) * vw + (l0 / kLG & 1);
+                    float2_t lo = {acc[0][a][c][j] * sc[0], acc[1][a][c][j] * sc[1]};
+                    float2_t hi = {acc[2][a][c][j] * sc[2], acc[3][a][c][j] * sc[3]};
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) {
+                        const uint2_t w = {
+                            __builtin_bit_cast(unsigned, __builtin_convertvector(lo, bf2_t)),
+                            __builtin_bit_cast(unsigned, __builtin_convertvector(hi, bf2_t))};
+                        y[q * ndg * 16 * vw] = w;
+                        lo[0] -= __builtin_bit_cast(float, w[0] << 16);
+                        lo[1] -= __builtin_bit_cast(float, w[0] & 0xffff0000u);
+                        hi[0] -= __builtin_bit_cast(float, w[1] << 16);
+                        hi[1] -= __builtin_bit_cast(float, w[1] & 0xffff0000u);
+                    }
+                }
+        }
+        return;
+    }
 #pragma unroll
     for (int l = 0; l < kLG; ++l) {
         if (l >= nl) break;
@@ -383,10 +427,10 @@ hipError_t launch_contract<float>(int64_t B, int Cin, int Cout, int K, bool kdeg
             4 * ((int64_t)(kTile - 1) * x_sb + (int64_t)Cin * K) >= (int64_t)kOutside ||
             w_sl < 0 || w_si < 0 || w_so < 0)
             return hipErrorNotSupported;
-        hipLaunchKernelGGL(k_contract_kdeg, dim3((unsigned)blocks), dim3(kThreadsC), 0, s, B,
+        hipLaunchKernelGGL(k_contract_kdeg<false>, dim3((unsigned)blocks), dim3(kThreadsC), 0, s, B,
                            Cin, Cout, K, otiles, lgroups, W, (unsigned)w_span, (int)w_sl,
                            (int)w_si, (int)w_so, X, (int)x_sb, Y, y_sb, y_so, y_sk, scale,
-                           accumulate);
+                           accumulate, nullptr, 0, 0, 0);
         return hipGetLastError();
     }
     const int64_t groups = (B + kTile - 1) / kTile;
@@ -410,6 +454,31 @@ hipError_t launch_contract<float>(int64_t B, int Cin, int Cout, int K, bool kdeg
         else CGTP_CONTRACT(false, 64);
     }
 #undef CGTP_CONTRACT
+    return hipGetLastError();
+}
+
+hipError_t launch_contract_edge_parts(int64_t B, int Cin, int Cout, int L, const float *W,
+                                      int64_t w_sl, int64_t w_si, int64_t w_so, const float *X,
+                                      void *Y, int R, int r0, int rend, const float *scale,
+                                      hipStream_t s)
+{
+    if (B == 0 || Cout == 0) return hipSuccess;
+    const int64_t groups = (B + kTile - 1) / kTile;
+    const int oend = rend - r0;
+    const int otiles = (oend + kTile - 1) / kTile;
+    const int lgroups = rt_groups(L - 1) * rt_vec_bytes(L - 1) / (2 * kLG);
+    const int64_t blocks = groups * otiles * lgroups;
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    const int64_t x_sb = (int64_t)Cin * L;
+    const int64_t w_span = 4 * ((L - 1) * w_sl + (int64_t)(Cin - 1) * w_si +
+                                (int64_t)(Cout - 1) * w_so + 1);
+    if (w_span >= (int64_t)kOutside || 4 * (int64_t)kTile * x_sb >= (int64_t)kOutside || w_sl < 0 ||
+        w_si < 0 || w_so < 0)
+        return hipErrorNotSupported;
+    hipLaunchKernelGGL(k_contract_kdeg<true>, dim3((unsigned)blocks), dim3(kThreadsC), 0, s, B, Cin,
+                       Cout, L, otiles, lgroups, W, (unsigned)w_span, (int)w_sl, (int)w_si,
+                       (int)w_so, X, (int)x_sb, nullptr, 0, 0, 0, scale, false,
+                       static_cast<uint2_t *>(Y), R / 16, r0, oend);
     return hipGetLastError();
 }
 

@@ -293,11 +293,16 @@ __device__ __forceinline__ void legendre_all_tab(const float *const *h, int g4,
     }
 }
 
-template <int LM, bool V1>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_sender_mfma(Tabs<float> tb, int R, int rb, int nc,
+// TILED (the value field alone, R a multiple of 16, rb 4, 8 or 16): SF in the tiles of 16 ranks
+// x 16 points that k_receiver_values reads, [B][R/16][UVs/16][64 lanes][4]. Rows then run rank
+// first, (u, q), so that a lane's four D rows are four consecutive ranks of one point: one
+// 16-byte store, 16 lanes writing 256 contiguous bytes.
+template <int LM, bool V1, bool TILED>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_sender_mfma(Tabs<float> tb, int R, int rb,
                                                      const float *__restrict__ H,
                                                      float *__restrict__ SF, int planes)
 {
+    static_assert(V1 || !TILED, "tiles hold the value field");
     using G = Grid<LM>;
     extern __shared__ float smem[];
     float4_t *cf = reinterpret_cast<float4_t *>(smem);  // [P] recurrence coefficients
@@ -320,7 +325,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
         // this lane's A-operand row (q, u); rows past the end compute on row 0 and are
         // never stored (a result row depends on its own A row only)
         const int ra = rt * 16 + n;
-        const int qa = ra < rows ? ra / G::U : 0, ua = ra < rows ? ra - qa * G::U : 0;
+        const int qr = TILED ? ra & (rb - 1) : ra / G::U;
+        const int ur = TILED ? ra / rb : ra - qr * G::U;
+        const int qa = ra < rows ? qr : 0, ua = ra < rows ? ur : 0;
         float seed[G::KM];
         load_seeds<LM>(tb, g4, ua, seed);
         LaneRows<LM, 1> c;
@@ -350,12 +357,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
             }
         }
         // D[(q,u) = 16 rt + 4 g + j][v = 16 t + n]
+        if constexpr (TILED) {
+            const int ro = rt * 16 + 4 * g4;
+            if (ro < rows) {  // rows is a multiple of 4
+                const int r = r0 + (ro & (rb - 1)), uo = ro / rb;
+                float *o = SF + (b * (R / 16) + r / 16) * (int64_t)(G::UVs * 16) + (r & 15) * 16;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int ro = rt * 16 + 4 * g4 + j;
-            if (ro < rows) {
-                const int qo = ro / G::U, uo = ro - qo * G::U;
-                if (nc == 0) {  // SF [B][R][3][UVs]
+                for (int t = 0; t < G::VT; ++t) {
+                    const int p = uo * G::V + t * 16 + n;
+                    if (t * 16 + n < G::V)
+                        *reinterpret_cast<float4_t *>(o + (p / 16) * 256 + (p & 15) * 4) = acc[0][t];
+                }
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int ro = rt * 16 + 4 * g4 + j;
+                if (ro < rows) {
+                    const int qo = ro / G::U, uo = ro - qo * G::U;
                     float *o = SF + (b * R + r0 + qo) * 3 * (int64_t)G::UVs + uo * G::V + n;
 #pragma unroll
                     for (int t = 0; t < G::VT; ++t) {
@@ -364,22 +383,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
                             if (!V1 && (planes & 2)) o[G::UVs + t * 16] = acc[1][t][j];
                             if (!V1 && (planes & 4)) o[2 * G::UVs + t * 16] = acc[2][t][j];
                             if (planes & 8) o[G::UVs + t * 16] = acc[0][t][j];
-                        }
-                    }
-                } else {  // SF [R/16][nc][B][16][3][64]
-                    const int r = r0 + qo;
-                    const int64_t nb = gridDim.x / nrb;  // B
-#pragma unroll
-                    for (int t = 0; t < G::VT; ++t) {
-                        const int p = uo * G::V + t * 16 + n;
-                        if (t * 16 + n < G::V) {
-                            const int c = p / kSfChunk, pp = p - c * kSfChunk;
-                            float *o = SF + ((((int64_t)(r >> 4) * nc + c) * nb + b) * 16 + (r & 15)) *
-                                                3 * kSfChunk + pp;
-                            if (planes & 1) o[0] = acc[0][t][j];
-                            if (!V1 && (planes & 2)) o[kSfChunk] = acc[1][t][j];
-                            if (!V1 && (planes & 4)) o[2 * kSfChunk] = acc[2][t][j];
-                            if (planes & 8) o[kSfChunk] = acc[0][t][j];
                         }
                     }
                 }
@@ -430,7 +433,11 @@ struct DenseSyn {
     static constexpr int NLA = (16 * G::K + NT - 1) / NT;  // tile loads per thread
 };
 
-template <int LM, bool V1>
+// TILED (with V1, R a multiple of 16): SF in the tiles k_receiver_values reads, one 16-row tile
+// of H being one rank tile of one node. The product is then formed as D[row][column], so a lane
+// holds four consecutive ranks of one point and a wave stores each 1 KB tile with one
+// instruction.
+template <int LM, bool V1, bool TILED>
 __global__ __launch_bounds__((64 * DenseSyn<LM, V1>::NW)) __attribute__((amdgpu_waves_per_eu(3))) void k_sender_dense(
     const float *__restrict__ Ys, int64_t rows, const float *__restrict__ H,
     float *__restrict__ SF, int planes)
@@ -491,10 +498,15 @@ __global__ __launch_bounds__((64 * DenseSyn<LM, V1>::NW)) __attribute__((amdgpu_
         for (int kk = 0; kk < D::KS; ++kk)
 #pragma unroll
             for (int t = 0; t < D::CTW; ++t)
-                acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(bq[t][kk], a[kk], acc[t], 0, 0, 0);
+                acc[t] = TILED ? __builtin_amdgcn_mfma_f32_16x16x4f32(a[kk], bq[t][kk], acc[t], 0, 0, 0)
+                               : __builtin_amdgcn_mfma_f32_16x16x4f32(bq[t][kk], a[kk], acc[t], 0, 0, 0);
         // D[column 16 t + 4 g + j][row n]: columns 4 g .. 4 g + 3 of row 16 rt + n
         const int64_t row = rt * 16 + n;
-        if (store && row < rows) {
+        if constexpr (TILED) {  // D[row 4 g + j][column n]; rows is a multiple of 16
+            float *dst = SF + (rt * (G::UVs / 16) + t0) * 256 + 4 * lane;
+#pragma unroll
+            for (int t = 0; t < D::CTW; ++t) *reinterpret_cast<float4_t *>(dst + 256 * t) = acc[t];
+        } else if (store && row < rows) {
             float *dst = SF + row * D::NCOL + pofs + t0 * 16 + 4 * g4;
 #pragma unroll
             for (int t = 0; t < D::CTW; ++t) *reinterpret_cast<float4_t *>(dst + 16 * t) = acc[t];
@@ -1112,7 +1124,7 @@ hipError_t onsite_lm(const Tabs<float> &tb, int64_t B, int R, const float *HA, c
 }
 
 // The dense synthesis as persistent workgroups, as many as the device holds at once.
-template <int LM, bool V1>
+template <int LM, bool V1, bool TILED>
 hipError_t launch_dense(const Tabs<float> &tb, int64_t rows, const float *H, float *SF, int planes,
                         hipStream_t s)
 {
@@ -1124,43 +1136,51 @@ hipError_t launch_dense(const Tabs<float> &tb, int64_t rows, const float *H, flo
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) !=
                 hipSuccess ||
             hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &per, reinterpret_cast<const void *>(&k_sender_dense<LM, V1>), 64 * D::NW, 0) !=
+                &per, reinterpret_cast<const void *>(&k_sender_dense<LM, V1, TILED>), 64 * D::NW, 0) !=
                 hipSuccess ||
             cus < 1 || per < 1)
             return kDenseSynthBlocks;
         return (int64_t)cus * per;
     }();
     const int64_t grid = ntiles < resident ? ntiles : resident;
-    hipLaunchKernelGGL((k_sender_dense<LM, V1>), dim3((unsigned)grid), dim3(64 * D::NW), 0, s,
+    hipLaunchKernelGGL((k_sender_dense<LM, V1, TILED>), dim3((unsigned)grid), dim3(64 * D::NW), 0, s,
                        tb.ysyn, rows, H, SF, planes);
     return hipGetLastError();
 }
 
+// tiled: the value field in the tiles of k_receiver_values (planes is then not used).
 template <int LM>
 hipError_t sender_lm(const Tabs<float> &tb, int64_t B, int R, const float *H, float *SF,
-                     bool chunked, hipStream_t s, int planes)
+                     bool tiled, hipStream_t s, int planes)
 {
     using G = Grid<LM>;
+    if (tiled && R % 16 != 0) return hipErrorInvalidValue;
+    if constexpr (LM >= 1 && LM <= kDenseSynthMaxL) {
+        if (tiled) return launch_dense<LM, true, true>(tb, B * R, H, SF, 1, s);
+        if (planes == 1 || planes == 8) return launch_dense<LM, true, false>(tb, B * R, H, SF, planes, s);
+        return launch_dense<LM, false, false>(tb, B * R, H, SF, planes, s);
+    }
     const size_t fixed = 4 * (size_t)G::P + 4 * (size_t)G::KM * G::QB;
-    const int rb = pick_rb(tb.d, R, fixed, G::HR);
+    int rb = pick_rb(tb.d, R, fixed, G::HR);
+    if (tiled) {  // a divisor of 16, three workgroups of four waves per compute unit
+        rb = 16;
+        while (rb > 4 && sizeof(float) * (fixed + rb * (size_t)G::HR) > (size_t)tb.d.lds_cu / 3) rb /= 2;
+        if (sizeof(float) * (fixed + rb * (size_t)G::HR) > (size_t)tb.d.lds_max)
+            return hipErrorNotSupported;
+    }
     if (rb < 1) return hipErrorNotSupported;
     const int64_t blocks = B * ((R + rb - 1) / rb);
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    if (chunked && R % 16 != 0) return hipErrorInvalidValue;
-    if constexpr (LM >= 1 && LM <= kDenseSynthMaxL) {
-        if (!chunked) {
-            if (planes == 1 || planes == 8) return launch_dense<LM, true>(tb, B * R, H, SF, planes, s);
-            return launch_dense<LM, false>(tb, B * R, H, SF, planes, s);
-        }
-    }
-    const int nc = chunked ? sf_chunks(tb.d) : 0;
     const dim3 grid((unsigned)blocks), block(64 * waves_for(rb * G::U));
     const size_t sh = sizeof(float) * (fixed + rb * (size_t)G::HR);
-    if ((planes & ~9) == 0)  // the value field alone (planes 0 and/or 1)
-        hipLaunchKernelGGL((k_sender_mfma<LM, true>), grid, block, sh, s, tb, R, rb, nc, H, SF,
+    if (tiled)
+        hipLaunchKernelGGL((k_sender_mfma<LM, true, true>), grid, block, sh, s, tb, R, rb, H, SF,
+                           planes);
+    else if ((planes & ~9) == 0)  // the value field alone (planes 0 and/or 1)
+        hipLaunchKernelGGL((k_sender_mfma<LM, true, false>), grid, block, sh, s, tb, R, rb, H, SF,
                            planes);
     else
-        hipLaunchKernelGGL((k_sender_mfma<LM, false>), grid, block, sh, s, tb, R, rb, nc, H, SF,
+        hipLaunchKernelGGL((k_sender_mfma<LM, false, false>), grid, block, sh, s, tb, R, rb, H, SF,
                            planes);
     return hipGetLastError();
 }
@@ -1203,13 +1223,13 @@ bool default_grid(const Dims &d)
 bool sender_mfma_supported(const Dims &d) { return default_grid(d) && d.lmax <= 24; }
 
 hipError_t launch_sender_mfma(const Tabs<float> &tb, int64_t B, int R, const float *H, float *SF,
-                              bool chunked, hipStream_t s, int planes)
+                              bool tiled, hipStream_t s, int planes)
 {
     if (B == 0) return hipSuccess;
     if (!sender_mfma_supported(tb.d)) return hipErrorNotSupported;
     switch (tb.d.lmax) {
 #define CGTP_CASE(LMV) \
-    case LMV: return sender_lm<LMV>(tb, B, R, H, SF, chunked, s, planes);
+    case LMV: return sender_lm<LMV>(tb, B, R, H, SF, tiled, s, planes);
         CGTP_LMAX_CASES(CGTP_CASE)
 #undef CGTP_CASE
     default: return hipErrorNotSupported;

@@ -100,6 +100,22 @@ hipError_t launch_contract<double>(int64_t, int, int, int, bool, const double *,
                                    int64_t, const double *, int64_t, double *, int64_t, int64_t,
                                    int64_t, const double *, bool, hipStream_t);
 
+// Edge coefficients of the values-only receiver (receiver_values.hip): the kdeg contraction
+// above (with scale) into ranks [r0, r0 + Cout) of Y [B][R/16][3][rt_groups][16 ranks][8] bf16,
+// each value as the exact sum of three bf16 parts, a slot vector holding 8 degrees of one part
+// (4 up to lmax 3; zero past lmax). Ranks [r0 + Cout, rend) are written as zeros.
+constexpr int kRtPart = 8;
+__host__ __device__ constexpr int rt_groups(int lmax) { return lmax / kRtPart + 1; }
+__host__ __device__ constexpr int rt_vec_bytes(int lmax) { return lmax < 4 ? 8 : 16; }
+inline size_t rt_parts_bytes(int lmax, int64_t E, int R)
+{
+    return (size_t)E * R * 3 * rt_groups(lmax) * rt_vec_bytes(lmax);
+}
+hipError_t launch_contract_edge_parts(int64_t B, int Cin, int Cout, int L, const float *W,
+                                      int64_t w_sl, int64_t w_si, int64_t w_so, const float *X,
+                                      void *Y, int R, int r0, int rend, const float *scale,
+                                      hipStream_t s);
+
 // fp32 contraction whose Cin = nsrc * xg.rows input rows come from nsrc sources: rows
 // [c rows, (c + 1) rows) of node b are xg.base[c] + b * x_sb + i * K (i < rows), otherwise as
 // launch_contract (never accumulating, no scale). rows must be a multiple of 32 and
@@ -251,15 +267,12 @@ hipError_t launch_analysis_folded(const Tabs<float> &tb, int64_t B, int R, const
 // (same output as launch_sender_fields) and the inverse transforms of S [N][R][2][UVs]
 // into Ta, Tb. hipErrorNotSupported when the grid is wider than their tiling
 // (V > 80) or the LDS staging does not fit.
-// With chunked set, SF is written in the layout the MFMA receiver reads:
-// [R/16][NC][B][16][3][64], NC = ceil(UV / 64) chunks of 64 grid points, so the fields a
-// receiver wave needs from one sender (16 ranks x 3 fields x 64 points) are one
-// contiguous 12 KiB run. Requires R % 16 == 0.
-constexpr int kSfChunk = 64;
-inline int sf_chunks(const Dims &d) { return (d.UV + kSfChunk - 1) / kSfChunk; }
+// With tiled set (R a multiple of 16) SF holds the value field alone, in the tiles that
+// launch_receiver_values reads: [B][R/16][UVs/16][64][4], each tile 16 ranks x 16 points with
+// lane 16 g + n holding ranks 4 g .. 4 g + 3 of point n.
 bool sender_mfma_supported(const Dims &d);
 hipError_t launch_sender_mfma(const Tabs<float> &tb, int64_t B, int R, const float *H, float *SF,
-                              bool chunked, hipStream_t s, int planes = 7);
+                              bool tiled, hipStream_t s, int planes = 7);
 // Inverse transforms on MFMA of the summed grid fields S [B][R][NF][UVs] into Ta, Tb
 // (default grid): mode 0, NF = 2 (Gaunt product, surface curl); mode 1, NF = 3 (Gaunt sum;
 // the curl's moved-derivative pair S1, S2); mode 2, NF = 6 (per output a value sum and a
@@ -280,15 +293,21 @@ constexpr int kMfmaRecvMinL = 7;  // three-plane form: below this the per-thread
 bool receiver_mfma_supported(const Dims &d, int R);
 // S [N][R][planes][UVs]: 2 planes, or with values_only 3 (6 with SFf).
 size_t receiver_mfma_ws_elems(const Dims &d, int64_t N, int R, int planes);
-// values_only (not with Rtg; default grid): the moved-derivative curl, reading only the value
-// plane of SF (and SFf); every lmax. Otherwise lmax >= kMfmaRecvMinL.
+// The three-plane form, lmax >= kMfmaRecvMinL.
 hipError_t launch_receiver_mfma(const Tabs<float> &tb, int64_t N, int R, const int32_t *row_ptr,
                                 const int32_t *col, const int32_t *order, const float *unit,
                                 const float *Rt, const float *Rtg, const float *SF,
-                                const float *SFf, bool sf_chunked, float *S, float *Ta, float *Tb,
-                                hipStream_t s, bool values_only = false, bool analyse = true);
-// The inverse transforms of the summed grid fields S of a receiver (analyse = false above)
-// into Ta, Tb: mode as launch_analysis_mfma; mode 0 also off the default grid.
+                                const float *SFf, float *S, hipStream_t s);
+// fp32 receiver pass that reads sender values only, in tiles (receiver_values.hip): the curl in
+// the moved-derivative form, every lmax, default grid, R a multiple of 16. Writes the summed
+// grid fields S [N][R][3][UVs] (six planes with SFf); the inverse transforms are the caller's.
+// SF, SFf: launch_sender_mfma's tiles; with Rtg a second plane (the curl factors' values)
+// follows SF's first at N R UVs elements.
+hipError_t launch_receiver_values(const Tabs<float> &tb, int64_t N, int R, const int32_t *row_ptr,
+                                  const int32_t *col, const int32_t *order, const float *unit,
+                                  const void *Rt, const void *Rtg, const float *SF,
+                                  const float *SFf, float *S, hipStream_t s);
+// The inverse transforms of the summed grid fields S of a receiver into Ta, Tb: mode as launch_analysis_mfma; mode 0 also off the default grid.
 hipError_t launch_summed_analysis(const Tabs<float> &tb, int64_t N, int R, const float *S,
                                   float *Ta, float *Tb, hipStream_t s, int mode);
 
@@ -300,11 +319,11 @@ hipError_t launch_summed_analysis(const Tabs<float> &tb, int64_t N, int R, const
 hipError_t launch_gather_probe(const Dims &d, int64_t N, int R, const int32_t *row_ptr,
                                const int32_t *col, const int32_t *order, const float *SF,
                                float *sink, hipStream_t s);
-// The same for the MFMA receiver in its values-only form on the plain sender layout
-// (receiver_mfma.hip): its blocks, block order and 16-byte value-plane loads.
-hipError_t launch_gather_probe_mfma(const Dims &d, int64_t N, int R, const int32_t *row_ptr,
-                                    const int32_t *col, const int32_t *order, const float *SF,
-                                    float *sink, hipStream_t s);
+// The same for launch_receiver_values (R a multiple of 16): its blocks, block order and
+// 16-byte loads of the value tiles SF [N][R/16][UVs/16][64][4].
+hipError_t launch_gather_probe_values(const Dims &d, int64_t N, int R, const int32_t *row_ptr,
+                                      const int32_t *col, const int32_t *order, const float *SF,
+                                      float *sink, hipStream_t s);
 
 // Status reporting shared by the entry points of every source file: report() stores the
 // detail message returned by cgtp_last_error() on this thread and passes the status through.

@@ -76,15 +76,24 @@ struct Layout {
     size_t wc = 0;           // concatenated factor blocks of a run of rank groups [L][C][R]
 };
 
-// Receiver on MFMA in its values-only form (the moved-derivative curl: only the senders'
-// values are read, plane 0, and with per-block factors (split) the curl factors' values in
-// plane 1): fp32, zonal edge field, R a multiple of 16, the default grid (for the MFMA
-// analysis of its moved planes); every lmax.
+// Message passing in the values-only form (the moved-derivative curl: only the senders' values
+// are read, with per-block factors (split) the Gaunt and the curl factors'): fp32, zonal edge
+// field, the default grid (for the MFMA analysis of its moved planes), more than 8 ranks (fewer
+// would fill less than a quarter of the receiver's two rank tiles; the per-thread receiver takes
+// them eight at a time); every lmax.
 bool mfma_values_only(const cgtp_plan_s *p, int R, bool split)
 {
     (void)split;
-    return p->dtype == CGTP_F32 && !(p->flags & CGTP_EDGE_SEPARATED) &&
-           cgtp::receiver_mfma_supported(p->d, R) && cgtp::sender_mfma_supported(p->d);
+    return p->dtype == CGTP_F32 && !(p->flags & CGTP_EDGE_SEPARATED) && R > 8 &&
+           cgtp::sender_mfma_supported(p->d);
+}
+
+// Ranks of the message-passing buffers: rounded up to the receiver's rank tiles in the
+// values-only form. The ranks added carry zero edge coefficients and are never projected; ranks
+// do not mix before the projection.
+int mp_rank(const cgtp_plan_s *p, int R, bool split)
+{
+    return mfma_values_only(p, R, split) ? (R + 15) / 16 * 16 : R;
 }
 
 // Receiver on MFMA: the values-only form above, else (three sender planes) fp32, zonal edge
@@ -104,15 +113,6 @@ bool values_only_form(const cgtp_plan_s *p, int R, bool split)
 {
     if (p->flags & CGTP_EDGE_SEPARATED) return false;
     return !use_mfma_receiver(p, R, split) || mfma_values_only(p, R, split);
-}
-
-// The MFMA receiver reads the sender fields in 64-point chunks when the MFMA sender writes
-// them (fp32, default grid, from kMfmaRecvMinL on; below it the dense sender writes the plain
-// layout).
-bool sf_chunked(const cgtp_plan_s *p, int R, bool split = false)
-{
-    return use_mfma_receiver(p, R, split) && p->d.lmax >= cgtp::kMfmaRecvMinL &&
-           cgtp::sender_mfma_supported(p->d);
 }
 
 // On-site workspace: HA, HB, Ta, Tb, each [N][R][K] (R: the plan's rank, or the total
@@ -158,10 +158,14 @@ Layout mp_layout(const cgtp_plan_s *p, int R, int64_t N, int64_t E, bool two = f
 {
     size_t es = p->dtype == CGTP_F64 ? 8 : 4;
     const size_t nh = (two || split) ? 2 : 1, nsf = two ? 2 : 1, nrt = split ? 2 : 1;
+    const size_t wc = align256(es * (size_t)p->d.L * p->C * R);
+    R = mp_rank(p, R, split);
     size_t h = align256(es * (size_t)N * R * p->d.K);
-    const size_t sf_pts = sf_chunked(p, R, split) ? (size_t)cgtp::sf_chunks(p->d) * cgtp::kSfChunk : p->d.UVs;
-    size_t sf = align256(es * (size_t)N * R * 3 * sf_pts);
-    size_t rt = align256(es * (size_t)E * R * p->d.L);
+    // values only: one plane of tiles (two with split factors); otherwise three fields
+    const size_t sf_planes = mfma_values_only(p, R, split) ? (split ? 2 : 1) : 3;
+    size_t sf = align256(es * (size_t)N * R * sf_planes * p->d.UVs);
+    size_t rt = align256(mfma_values_only(p, R, split) ? cgtp::rt_parts_bytes(p->d.lmax, E, R)
+                                                       : es * (size_t)E * R * p->d.L);
     const int sg_planes = values_only_form(p, R, split) ? (two ? 6 : 3) : 2;
     size_t sg = use_mfma_receiver(p, R, split)
                     ? align256(es * cgtp::receiver_mfma_ws_elems(p->d, N, R, sg_planes))
@@ -176,7 +180,7 @@ Layout mp_layout(const cgtp_plan_s *p, int R, int64_t N, int64_t E, bool two = f
     l.off[4] = l.off[3] + h;
     l.off[5] = l.off[4] + h;
     l.wc = l.off[5] + sg;  // the output weights of a sector's groups, concatenated
-    l.total = l.wc + align256(es * (size_t)p->d.L * p->C * R);
+    l.total = l.wc + wc;
     l.hf = h;
     l.sff = sf;
     l.rtf = rt;
@@ -437,7 +441,7 @@ int run_mp(cgtp_plan_s *p, int op, int64_t N, int64_t E, const int32_t *row_ptr,
            char *ws, hipStream_t s)
 {
     const cgtp::Dims &d = p->d;
-    const int C = p->C, R = p->R;
+    const int C = p->C, R = p->R, Rp = mp_rank(p, R, false);
     const bool separated = (p->flags & CGTP_EDGE_SEPARATED) != 0;
     const bool two = If != nullptr;
     cgtp::Tabs<T> tb = cgtp::bind_tables<T>(d, p->tables);
@@ -449,7 +453,7 @@ int run_mp(cgtp_plan_s *p, int op, int64_t N, int64_t E, const int32_t *row_ptr,
     T *Tb = reinterpret_cast<T *>(ws + lay.off[4]);
     T *HIf = two ? reinterpret_cast<T *>(ws + lay.off[0] + lay.hf) : nullptr;
     T *SFf = two ? reinterpret_cast<T *>(ws + lay.off[1] + lay.sff) : nullptr;
-    const int64_t hs = (int64_t)R * d.K;
+    const int64_t hs = (int64_t)Rp * d.K;
     // the zonal receiver takes the curl in the moved-derivative form: the senders' value plane
     // is all it reads
     const bool values_only = values_only_form(p, R, false);
@@ -468,21 +472,26 @@ int run_mp(cgtp_plan_s *p, int op, int64_t N, int64_t E, const int32_t *row_ptr,
         T *h = slot ? HIf : HI, *sf = slot ? SFf : SF;
         const int planes = values_only ? 1 : 7;
         if constexpr (sizeof(T) == 4) {
-            if (sf_chunked(p, R))
-                e = cgtp::launch_sender_mfma(tb, N, R, h, sf, true, s, planes);
+            if (mfma_values_only(p, R, false))
+                e = cgtp::launch_sender_mfma(tb, N, Rp, h, sf, true, s);
             else
-                e = cgtp::launch_sender_fields<T>(tb, N, R, h, sf, s, planes);
+                e = cgtp::launch_sender_fields<T>(tb, N, Rp, h, sf, s, planes);
         } else {
-            e = cgtp::launch_sender_fields<T>(tb, N, R, h, sf, s, planes);
+            e = cgtp::launch_sender_fields<T>(tb, N, Rp, h, sf, s, planes);
         }
         if (e != hipSuccess) return hip_fail(e, "sender fields");
     }
     rec.mark();
     // Eq. msgpass-tildeR into Rt [E][L][R] (the zonal form folds in the addition-theorem
     // weight (2l+1)/(4 pi))
-    e = cgtp::launch_contract<T>(E, C, R, d.L, true, (const T *)UE, (int64_t)C * R, R, 1,
-                                 (const T *)rad, (int64_t)C * d.L, Rt, (int64_t)d.L * R, 1, R,
-                                 separated ? nullptr : tb.cl, false, s);
+    if (mfma_values_only(p, R, false))
+        e = cgtp::launch_contract_edge_parts(E, C, R, d.L, (const float *)UE, (int64_t)C * R, R, 1,
+                                             (const float *)rad, Rt, Rp, 0, Rp,
+                                             (const float *)tb.cl, s);
+    else
+        e = cgtp::launch_contract<T>(E, C, R, d.L, true, (const T *)UE, (int64_t)C * R, R, 1,
+                                     (const T *)rad, (int64_t)C * d.L, Rt, (int64_t)d.L * R, 1, R,
+                                     separated ? nullptr : tb.cl, false, s);
     if (e != hipSuccess) return hip_fail(e, "contract edge radial");
     rec.mark();
     {
@@ -494,9 +503,13 @@ int run_mp(cgtp_plan_s *p, int op, int64_t N, int64_t E, const int32_t *row_ptr,
         if constexpr (sizeof(T) == 4) {
             mfma = use_mfma_receiver(p, R);
             if (mfma) {
-                e = cgtp::launch_receiver_mfma(tb, N, R, row_ptr, col, p->order,
-                                               (const float *)unit, Rt, nullptr, SF, SFf,
-                                               sf_chunked(p, R), Sg, Ta, Tb, s, values_only, false);
+                e = values_only
+                        ? cgtp::launch_receiver_values(tb, N, Rp, row_ptr, col, p->order,
+                                                       (const float *)unit, Rt, nullptr, SF, SFf,
+                                                       Sg, s)
+                        : cgtp::launch_receiver_mfma(tb, N, R, row_ptr, col, p->order,
+                                                     (const float *)unit, Rt, nullptr, SF, SFf, Sg,
+                                                     s);
                 if (e != hipSuccess) return hip_fail(e, "receiver (mfma)");
                 amode = values_only ? (two ? 2 : 1) : 0;
             }
@@ -512,7 +525,7 @@ int run_mp(cgtp_plan_s *p, int op, int64_t N, int64_t E, const int32_t *row_ptr,
         rec.mark();
         if constexpr (sizeof(T) == 4) {
             if (amode >= 0) {
-                e = cgtp::launch_summed_analysis(tb, N, R, Sg, Ta, Tb, s, amode);
+                e = cgtp::launch_summed_analysis(tb, N, Rp, Sg, Ta, Tb, s, amode);
                 if (e != hipSuccess) return hip_fail(e, "analysis");
             }
         }
@@ -623,16 +636,15 @@ Factors resolve_factors(const cgtp_plan_s *p, int in_blocks, const void *U1, con
 // Projection of each output sector (Eqs. cat-alpha-phi, cat-beta-phi): the sum over the
 // groups' products that feed one of its blocks, each with that block's weights. fp32 with
 // R a multiple of 32: one contraction per sector over all of its contributions, the rows
-// gathered from Ta / Tb and the weights concatenated along the rank into wcat [L][C][n R];
+// gathered from Ta / Tb (row stride rs) and the weights concatenated along the rank into wcat [L][C][n R];
 // otherwise one accumulating contraction per contribution.
 template <typename T>
 int project_blocks(const cgtp_plan_s *p, const Groups &G, int64_t N, const Factors &f,
-                   const T *Ta, const T *Tb, void *oe, void *oo, T *wcat, hipStream_t s,
+                   const T *Ta, const T *Tb, int64_t rs, void *oe, void *oo, T *wcat, hipStream_t s,
                    StageRec &rec)
 {
     const cgtp::Dims &d = p->d;
     const int C = p->C, R = p->R;
-    const int64_t rs = (int64_t)G.n * R * d.K;  // row stride of Ta / Tb
     const size_t es = sizeof(T);
     void *outs[2] = {oe, oo};
     for (int sec = 0; sec < 2; ++sec) {
@@ -747,13 +759,13 @@ int run_onsite_groups(cgtp_plan_s *p, const Groups &G, int64_t N, const void *co
             e = cgtp::launch_onsite_folded(tb, N, Rg, HA, HB, Ta, Tb, s, HAc, HBc);
             if (e != hipSuccess) return hip_fail(e, "onsite grid (split)");
             rec.mark();
-            return project_blocks<T>(p, G, N, f, Ta, Tb, oe, oo, wc, s, rec);
+            return project_blocks<T>(p, G, N, f, Ta, Tb, (int64_t)Rg * d.K, oe, oo, wc, s, rec);
         }
     }
     e = cgtp::launch_onsite_grid<T>(tb, N, Rg, HA, HB, Ta, Tb, s);
     if (e != hipSuccess) return hip_fail(e, "onsite grid");
     rec.mark();
-    return project_blocks<T>(p, G, N, f, Ta, Tb, oe, oo, wc, s, rec);
+    return project_blocks<T>(p, G, N, f, Ta, Tb, (int64_t)Rg * d.K, oe, oo, wc, s, rec);
 }
 
 template <typename T>
@@ -762,10 +774,10 @@ int run_mp_groups(cgtp_plan_s *p, const Groups &G, int64_t N, int64_t E, const i
                   const Factors &f, void *oe, void *oo, char *ws, hipStream_t s)
 {
     const cgtp::Dims &d = p->d;
-    const int C = p->C, R = p->R, Rg = G.n * R;
+    const int C = p->C, R = p->R, Rs = G.n * R, Rg = mp_rank(p, Rs, G.split);
     const bool separated = (p->flags & CGTP_EDGE_SEPARATED) != 0;
     cgtp::Tabs<T> tb = cgtp::bind_tables<T>(d, p->tables);
-    Layout lay = mp_layout(p, Rg, N, E, false, G.split);
+    Layout lay = mp_layout(p, Rs, N, E, false, G.split);
     T *wc = reinterpret_cast<T *>(ws + lay.wc);
     T *HI = reinterpret_cast<T *>(ws + lay.off[0]);
     T *SF = reinterpret_cast<T *>(ws + lay.off[1]);
@@ -792,14 +804,15 @@ int run_mp_groups(cgtp_plan_s *p, const Groups &G, int64_t N, int64_t E, const i
     // split: the Gaunt factors' contraction gives the sender values (plane 0); the curl
     // factors' give the two derivative fields (planes 1, 2), or in the moved-derivative form
     // their values (plane 1)
-    const bool values_only = values_only_form(p, Rg, G.split);
+    const bool values_only = values_only_form(p, Rs, G.split);
     for (int pass = 0; pass < (G.split ? 2 : 1); ++pass) {
         const T *h = pass ? HIc : HI;
         const int planes =
             G.split ? (pass ? (values_only ? 8 : 6) : 1) : (values_only ? 1 : 7);
         if constexpr (sizeof(T) == 4) {
-            if (sf_chunked(p, Rg, G.split))
-                e = cgtp::launch_sender_mfma(tb, N, Rg, h, SF, true, s, planes);
+            if (mfma_values_only(p, Rs, G.split))
+                e = cgtp::launch_sender_mfma(tb, N, Rg, h,
+                                             SF + (pass ? (int64_t)N * Rg * d.UVs : 0), true, s);
             else
                 e = cgtp::launch_sender_fields<T>(tb, N, Rg, h, SF, s, planes);
         } else {
@@ -812,10 +825,19 @@ int run_mp_groups(cgtp_plan_s *p, const Groups &G, int64_t N, int64_t E, const i
         const Group &g = G.g[gi];
         for (int pass = 0; pass < (G.split ? 2 : 1); ++pass) {
             const int blk = G.split ? (pass ? g.bc : g.bg) : group_block(g);
-            e = cgtp::launch_contract<T>(E, C, R, d.L, true, (const T *)f.in1[blk],
-                                         (int64_t)C * R, R, 1, (const T *)rad, (int64_t)C * d.L,
-                                         (pass ? Rtc : Rt) + (int64_t)gi * R, (int64_t)d.L * Rg,
-                                         1, Rg, separated ? nullptr : tb.cl, false, s);
+            if (mfma_values_only(p, Rs, G.split))
+                e = cgtp::launch_contract_edge_parts(E, C, R, d.L, (const float *)f.in1[blk],
+                                                     (int64_t)C * R, R, 1, (const float *)rad,
+                                                     pass ? Rtc : Rt, Rg, gi * R,
+                                                     gi + 1 < G.n ? (gi + 1) * R : Rg,
+                                                     (const float *)tb.cl, s);
+            else
+                e = cgtp::launch_contract<T>(E, C, R, d.L, true, (const T *)f.in1[blk],
+                                             (int64_t)C * R, R, 1, (const T *)rad,
+                                             (int64_t)C * d.L,
+                                             (pass ? Rtc : Rt) + (int64_t)gi * R,
+                                             (int64_t)d.L * Rg, 1, Rg,
+                                             separated ? nullptr : tb.cl, false, s);
             if (e != hipSuccess) return hip_fail(e, "contract edge radial");
         }
     }
@@ -826,17 +848,19 @@ int run_mp_groups(cgtp_plan_s *p, const Groups &G, int64_t N, int64_t E, const i
     int amode = -1;  // analysis mode of S (launch_analysis_mfma), -1: none
     bool mfma = false;
     if constexpr (sizeof(T) == 4) {
-        mfma = use_mfma_receiver(p, Rg, G.split);
+        mfma = use_mfma_receiver(p, Rs, G.split);
         if (mfma) {
-            e = cgtp::launch_receiver_mfma(tb, N, Rg, row_ptr, col, p->order, (const float *)unit,
-                                           Rt, Rtc, SF, nullptr, sf_chunked(p, Rg, G.split), Sg, Ta,
-                                           Tb, s, values_only, false);
+            e = values_only
+                    ? cgtp::launch_receiver_values(tb, N, Rg, row_ptr, col, p->order,
+                                                   (const float *)unit, Rt, Rtc, SF, nullptr, Sg, s)
+                    : cgtp::launch_receiver_mfma(tb, N, Rg, row_ptr, col, p->order,
+                                                 (const float *)unit, Rt, Rtc, SF, nullptr, Sg, s);
             if (e != hipSuccess) return hip_fail(e, "receiver (mfma)");
             amode = values_only ? 1 : 0;
         }
     }
     if (!mfma) {
-        const bool hand_over = values_only && zonal_mfma_analysis(p, Rg, G.split);
+        const bool hand_over = values_only && zonal_mfma_analysis(p, Rs, G.split);
         e = cgtp::launch_receiver<T>(tb, separated, N, Rg, row_ptr, col, p->order,
                                      (const T *)unit, Rt, Rtc, SF, nullptr, Ta, Tb, s, values_only,
                                      hand_over ? Sg : nullptr, false);
@@ -851,7 +875,7 @@ int run_mp_groups(cgtp_plan_s *p, const Groups &G, int64_t N, int64_t E, const i
         }
     }
     rec.mark();
-    return project_blocks<T>(p, G, N, f, Ta, Tb, oe, oo, wc, s, rec);
+    return project_blocks<T>(p, G, N, f, Ta, Tb, (int64_t)Rg * d.K, oe, oo, wc, s, rec);
 }
 
 // Message passing with two parity-bearing fields (Eq. twoparity-phi): rank groups as for
@@ -909,7 +933,7 @@ int run_mp_fields(cgtp_plan_s *p, const Groups &G, int64_t N, int64_t E, const i
             e = cgtp::launch_summed_analysis(tb, N, Rg, Sg, Ta, Tb, s, 1);
             if (e != hipSuccess) return hip_fail(e, "analysis");
             rec.mark();
-            return project_blocks<T>(p, G, N, f, Ta, Tb, oe, oo, wc, s, rec);
+            return project_blocks<T>(p, G, N, f, Ta, Tb, (int64_t)Rg * d.K, oe, oo, wc, s, rec);
         }
     }
     e = cgtp::launch_receiver_fields<T>(tb, N, Rg, row_ptr, col, p->order, HE, SF, Ta, Tb, s);
@@ -921,7 +945,7 @@ int run_mp_fields(cgtp_plan_s *p, const Groups &G, int64_t N, int64_t E, const i
     if (e != hipSuccess) return hip_fail(e, "receiver (edge field)");
     rec.mark();
     rec.mark();  // the analysis ran inside the receiver
-    return project_blocks<T>(p, G, N, f, Ta, Tb, oe, oo, wc, s, rec);
+    return project_blocks<T>(p, G, N, f, Ta, Tb, (int64_t)Rg * d.K, oe, oo, wc, s, rec);
 }
 
 // nu-body on-site product: one channel contraction per distinct (operand, factor) pair,
@@ -1507,10 +1531,13 @@ int cgtp_gather_probe(cgtp_plan plan, int64_t n_nodes, int64_t n_edges, const in
     if (!plan) return fail(CGTP_ERR_ARG, "plan is NULL");
     if (n_nodes < 0 || n_edges < 0 || n_edges >= 0x7fffffffLL)
         return fail(CGTP_ERR_ARG, "bad sizes");
-    // the receiver of cgtp_message_pass on this plan: the MFMA one in its values-only form on
-    // the plain sender layout, or the per-thread zonal one
+    // the receiver of cgtp_message_pass on this plan: the MFMA one in its values-only form (the
+    // probe covers its lower degrees, and ranks that are no multiple of 16 on grids of at most
+    // 1024 points), or the per-thread zonal one
     const bool mfma = use_mfma_receiver(plan, plan->R);
-    const bool mfma_plain = mfma && mfma_values_only(plan, plan->R, false) && !sf_chunked(plan, plan->R);
+    const bool mfma_plain = mfma && mfma_values_only(plan, plan->R, false) &&
+                            (plan->d.lmax < cgtp::kMfmaRecvMinL ||
+                             (plan->R % 16 != 0 && plan->d.UV <= 1024));
     if (plan->dtype != CGTP_F32 || (plan->flags & CGTP_EDGE_SEPARATED) || (mfma && !mfma_plain) ||
         (!mfma && plan->d.UV > 1024))
         return fail(CGTP_ERR_UNSUPPORTED,
@@ -1527,11 +1554,12 @@ int cgtp_gather_probe(cgtp_plan plan, int64_t n_nodes, int64_t n_edges, const in
     if (!st) st = check_order(plan, n_nodes);
     if (st) return st;
     hipError_t e =
-        mfma_plain ? cgtp::launch_gather_probe_mfma(plan->d, n_nodes, plan->R, row_ptr, col,
-                                                    plan->order,
-                                                    static_cast<const float *>(fields),
-                                                    static_cast<float *>(sink),
-                                                    static_cast<hipStream_t>(stream))
+        mfma_plain ? cgtp::launch_gather_probe_values(plan->d, n_nodes,
+                                                      mp_rank(plan, plan->R, false), row_ptr, col,
+                                                      plan->order,
+                                                      static_cast<const float *>(fields),
+                                                      static_cast<float *>(sink),
+                                                      static_cast<hipStream_t>(stream))
                    : cgtp::launch_gather_probe(plan->d, n_nodes, plan->R, row_ptr, col,
                                                plan->order, static_cast<const float *>(fields),
                                                static_cast<float *>(sink),

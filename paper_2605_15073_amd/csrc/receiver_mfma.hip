@@ -13,11 +13,8 @@
 // registers. The summed grid fields go to S [N][R][2][UVs]; the folded analysis
 // (k_analysis_rows when it does not fit)
 // then runs the inverse transforms (Eqs. msgpass-Tmu, msgpass-Tlm).
-// With VAL the surface curl takes the moved-derivative form (integration by parts on the
-// sphere: the curl's coefficient is the analysis of S1 = sum_j B_j dA_j/dx against dY/dphi
-// minus that of S2 = sum_j B_j dA_j/dphi against dY/dx): a lane reads only the value plane of
-// its sender fields and accumulates the Gaunt sum a B and the pair (S1, S2); S is then
-// [N][R][3][UVs] (six planes with two node slots) for the MFMA analysis in its moved modes.
+// This is the form for grids off the default one (from kMfmaRecvMinL up): the senders carry
+// three planes (A, dA/dx, dA/dphi). On the default grid k_receiver_values takes its place.
 #include "internal.h"
 
 namespace cgtp {
@@ -57,19 +54,6 @@ constexpr int recv_lds_floats(int lm)
     return 4 * (ks + ksg) * 64 + 2 * 64;
 }
 
-// Waves per SIMD the register allocation of k_receiver_mfma aims at (values-only form), at
-// least: 4 with one set of sums at lmax 3 to 7 (where it needs no spill), else 3 (2 at lmax
-// 24), and 2 with six sums (two node slots) or two coefficient sets from lmax 9 (which would
-// spill at 3).
-template <bool VAL, bool TWO, bool SPLIT>
-constexpr int kRecvWaves(int lm)
-{
-    return !VAL ? 1
-           : TWO ? 2
-           : SPLIT ? (lm >= 9 ? 2 : 3)
-                   : (lm >= 3 && lm <= 7 ? 4 : lm >= 24 ? 2 : 3);
-}
-
 // LM is lmax: the recurrence is unrolled with compile-time coefficients. A workgroup
 // is WPB waves; each wave owns PW = 64 grid points, one per lane: per edge a lane runs
 // the Legendre recurrence for P_l and P_l' at its own point (both in the same lane) into
@@ -80,11 +64,8 @@ constexpr int kRecvWaves(int lm)
 // product S_beta's. Its six sums keep it at 2 waves per SIMD.
 // SPLIT: the curl product's edge coefficients are Rtg (its own CP factors): the derivative
 // sum g multiplies P' with those, the value sum a P with Rt.
-// VAL: value planes only, moved-derivative curl (above). With SPLIT the senders carry the
-// Gaunt factors' values in plane 0 and the curl factors' in plane 1.
-template <int WPB, int LM, bool TWO, bool SPLIT, bool VAL>
-__global__ __launch_bounds__(64 * WPB)
-__attribute__((amdgpu_waves_per_eu(kRecvWaves<VAL, TWO, SPLIT>(LM)))) void k_receiver_mfma(Tabs<float> tb, int R, int nchunks,
+template <int WPB, int LM, bool TWO, bool SPLIT>
+__global__ __launch_bounds__(64 * WPB) void k_receiver_mfma(Tabs<float> tb, int R, int nchunks,
                                                             int64_t N,
                                                             const int32_t *__restrict__ row_ptr,
                                                             const int32_t *__restrict__ col,
@@ -94,7 +75,7 @@ __attribute__((amdgpu_waves_per_eu(kRecvWaves<VAL, TWO, SPLIT>(LM)))) void k_rec
                                                             const float *__restrict__ Rtg,
                                                             const float *__restrict__ SF,
                                                             const float *__restrict__ SFf,
-                                                            int sf_nc, float *__restrict__ S)
+                                                            float *__restrict__ S)
 {
     constexpr int TPW = 4;           // 16-point tiles per wave
     constexpr int PW = 16 * TPW;     // grid points per wave: one per lane
@@ -145,28 +126,19 @@ __attribute__((amdgpu_waves_per_eu(kRecvWaves<VAL, TWO, SPLIT>(LM)))) void k_rec
 
     // D[row = point 4 g + j][col = rank n]: a lane holds 4 consecutive points of one
     // rank, so its sender values are 16-byte loads and its S values 16-byte stores.
-    // VAL: sa, sb the Gaunt sums into S_alpha, S_beta; (ca1, ca2) the moved curl pair into
-    // S_alpha (the flipped slot's, TWO), (cb1, cb2) into S_beta (the natural slot's)
-    float4_t sa[TPW], sb[TPW], ca1[TPW], ca2[TPW], cb1[TPW], cb2[TPW];
+    float4_t sa[TPW], sb[TPW];
 #pragma unroll
     for (int t = 0; t < TPW; ++t) {
         sa[t] = float4_t{0.f, 0.f, 0.f, 0.f};
         sb[t] = float4_t{0.f, 0.f, 0.f, 0.f};
-        ca1[t] = ca2[t] = cb1[t] = cb2[t] = float4_t{0.f, 0.f, 0.f, 0.f};
     }
     // lane's points: pw0 + 16 t + 4 g + (0..3); lane's rank: r0 + n. The sender fields are
-    // either SF [N][R][3][UVs] (a sender's 16-rank block is [16][3][UVs]) or, with sf_nc
-    // chunks, SF [R/16][sf_nc][N][16][3][64] (this wave's 64 points of a sender are one
-    // contiguous [16][3][64] run).
-    const int fstride = sf_nc ? kSfChunk : UVs;  // field stride, elements
-    const unsigned voff = sf_nc ? (unsigned)((n * 3 * kSfChunk + 4 * g) * 4)
-                                : (unsigned)((n * 3 * UVs + pw0 + 4 * g) * 4);
-    const int64_t sfo = sf_nc ? ((int64_t)(r0 / kRT) * sf_nc + pw0 / kSfChunk) * N * (kRT * 3 * kSfChunk)
-                              : (int64_t)r0 * 3 * UVs;
-    const float *sfb = SF + sfo;
-    const float *sfbf = (TWO ? SFf : SF) + sfo;
-    const int64_t jstride = sf_nc ? (int64_t)kRT * 3 * kSfChunk : (int64_t)R * 3 * UVs;
-    const unsigned sfbytes = (unsigned)(kRT * 3 * fstride * 4);
+    // SF [N][R][3][UVs] (a sender's 16-rank block is [16][3][UVs]).
+    const unsigned voff = (unsigned)((n * 3 * UVs + pw0 + 4 * g) * 4);
+    const float *sfb = SF + (int64_t)r0 * 3 * UVs;
+    const float *sfbf = (TWO ? SFf : SF) + (int64_t)r0 * 3 * UVs;
+    const int64_t jstride = (int64_t)R * 3 * UVs;
+    const unsigned sfbytes = (unsigned)(kRT * 3 * UVs * 4);
     const int e0 = row_ptr[i], e1 = row_ptr[i + 1];
     // lanes whose 4 points all lie past the grid (the padding of the last chunk: up to 18% of
     // the points at lmax 7-8) load through an offset past the resource, which returns zeros
@@ -203,8 +175,8 @@ __attribute__((amdgpu_waves_per_eu(kRecvWaves<VAL, TWO, SPLIT>(LM)))) void k_rec
         for (int t = 0; t < TPW; ++t) {
             const unsigned so = (unsigned)(t * 16 * 4);
             fI[t] = bload4(sfr, vofft[t], so);
-            if (!VAL || SPLIT) fX[t] = bload4(sfr, vofft[t], so + fstride * 4);
-            if (!VAL) fP[t] = bload4(sfr, vofft[t], so + 2 * fstride * 4);
+            fX[t] = bload4(sfr, vofft[t], so + UVs * 4);
+            fP[t] = bload4(sfr, vofft[t], so + 2 * UVs * 4);
         }
     };
     // B operands: Rt[e][4 kk + g][r0 + n] for the value sum; for the derivative sum the rows
@@ -306,108 +278,32 @@ __attribute__((amdgpu_waves_per_eu(kRecvWaves<VAL, TWO, SPLIT>(LM)))) void k_rec
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) {
                 const float dxt = dx4[jj], dpt = dp4[jj];
-                if (VAL) {
-                    // dA/dx = g dxt and dA/dphi = g dpt of the edge field
-                    sa[t][jj] += a[jj] * fI[t][jj];
-                    // SPLIT: the curl takes the curl factors' values (plane 1)
-                    const float gf = gg[jj] * (SPLIT ? fX[t][jj] : fI[t][jj]);
-                    cb1[t][jj] += dxt * gf;
-                    cb2[t][jj] += dpt * gf;
-                    if (TWO) {
-                        sb[t][jj] += a[jj] * hI[t][jj];
-                        const float gh = gg[jj] * hI[t][jj];
-                        ca1[t][jj] += dxt * gh;
-                        ca2[t][jj] += dpt * gh;
-                    }
-                } else {
-                    sa[t][jj] += a[jj] * fI[t][jj];
-                    sb[t][jj] += gg[jj] * (dpt * fX[t][jj] - dxt * fP[t][jj]);
-                    if (TWO) {
-                        sa[t][jj] += gg[jj] * (dpt * hX[t][jj] - dxt * hP[t][jj]);
-                        sb[t][jj] += a[jj] * hI[t][jj];
-                    }
+                sa[t][jj] += a[jj] * fI[t][jj];
+                sb[t][jj] += gg[jj] * (dpt * fX[t][jj] - dxt * fP[t][jj]);
+                if (TWO) {
+                    sa[t][jj] += gg[jj] * (dpt * hX[t][jj] - dxt * hP[t][jj]);
+                    sb[t][jj] += a[jj] * hI[t][jj];
                 }
             }
         }
     }
-    // S[i][r0 + n][plane][p .. p + 3]: planes (S_alpha, S_beta), or with VAL the Gaunt sum and
-    // moved pair (sa, cb1, cb2), with two slots (sa, ca1, ca2, sb, cb1, cb2)
-    constexpr int NF = VAL ? (TWO ? 6 : 3) : 2;
+    // S[i][r0 + n][plane][p .. p + 3]: planes (S_alpha, S_beta)
 #pragma unroll
     for (int t = 0; t < TPW; ++t) {
         const int p = pw0 + 16 * t + 4 * g;
-        float *o = S + ((i * R + r0 + n) * NF) * (int64_t)UVs + p;
-        float4_t pl[NF];
-        if (!VAL) {
-            pl[0] = sa[t];
-            pl[1] = sb[t];
-        } else if (!TWO) {
-            pl[0] = sa[t];
-            pl[1] = cb1[t];
-            pl[2] = cb2[t];
-        } else {
-            pl[0] = sa[t];
-            pl[1] = ca1[t];
-            pl[2] = ca2[t];
-            pl[3] = sb[t];
-            pl[4] = cb1[t];
-            pl[5] = cb2[t];
-        }
+        float *o = S + ((i * R + r0 + n) * 2) * (int64_t)UVs + p;
         if (p + 3 < UV) {
-#pragma unroll
-            for (int f = 0; f < NF; ++f) *reinterpret_cast<float4_t *>(o + f * UVs) = pl[f];
+            *reinterpret_cast<float4_t *>(o) = sa[t];
+            *reinterpret_cast<float4_t *>(o + UVs) = sb[t];
         } else {
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj)
                 if (p + jj < UV) {
-#pragma unroll
-                    for (int f = 0; f < NF; ++f) o[f * UVs + jj] = pl[f][jj];
+                    o[jj] = sa[t][jj];
+                    o[UVs + jj] = sb[t][jj];
                 }
         }
     }
-}
-
-// Read-pattern ceiling of k_receiver_mfma in its values-only form on the plain sender layout
-// [N][R][3][UVs]: the same blocks in the same order, the same wave-uniform sender index per
-// edge and the same 16-byte loads of the value plane (one per 16-point tile and lane), with
-// nothing computed from them but a running sum; sink receives a value only if that sum equals
-// a constant no finite input sums to by chance, which keeps every load live.
-template <int WPB>
-__global__ __launch_bounds__(64 * WPB) void k_gather_probe_mfma(int UV, int UVs, int R,
-                                                                int nchunks, int64_t N,
-                                                                const int32_t *__restrict__ row_ptr,
-                                                                const int32_t *__restrict__ col,
-                                                                const int32_t *__restrict__ order,
-                                                                const float *__restrict__ SF,
-                                                                float *__restrict__ sink)
-{
-    constexpr int TPW = 4, PW = 16 * TPW, PC = WPB * PW;
-    // the wave index, uniform across the wave (so the buffer resources built from it are too)
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int g = lane >> 4, n = lane & 15;
-    int64_t slice, i;
-    if (!recv_block(N, order, slice, i)) return;
-    const int rest = (int)slice;
-    const int r0 = (rest / nchunks) * kRT;
-    const int pw0 = (rest % nchunks) * PC + wave * PW;
-    if (pw0 >= UV) return;
-    const unsigned voff = (unsigned)((n * 3 * UVs + pw0 + 4 * g) * 4);
-    unsigned vofft[TPW];
-#pragma unroll
-    for (int t = 0; t < TPW; ++t) vofft[t] = pw0 + 16 * t + 4 * g < UV ? voff : 0x80000000u;
-    const float *sfb = SF + (int64_t)r0 * 3 * UVs;
-    const int64_t jstride = (int64_t)R * 3 * UVs;
-    const unsigned sfbytes = (unsigned)(kRT * 3 * UVs * 4);
-    float4_t acc = float4_t{0.f, 0.f, 0.f, 0.f};
-    const int e0 = row_ptr[i], e1 = row_ptr[i + 1];
-    for (int e = e0; e < e1; ++e) {
-        const int64_t j = __builtin_amdgcn_readfirstlane(col[e]);
-        const __amdgpu_buffer_rsrc_t sfr = rsrc(sfb + j * jstride, sfbytes);
-#pragma unroll
-        for (int t = 0; t < TPW; ++t) acc += bload4(sfr, vofft[t], (unsigned)(t * 16 * 4));
-    }
-    const float sum = acc[0] + acc[1] + acc[2] + acc[3];
-    if (sum == -1.2345678e30f) sink[0] = sum;
 }
 
 // Inverse transforms of stored grid fields S [B][R][2][UVs] -> Ta, Tb [B][R][K]:
@@ -471,21 +367,6 @@ bool receiver_mfma_supported(const Dims &d, int R)
     return R % kRT == 0 && d.L <= 32;
 }
 
-hipError_t launch_gather_probe_mfma(const Dims &d, int64_t N, int R, const int32_t *row_ptr,
-                                    const int32_t *col, const int32_t *order, const float *SF,
-                                    float *sink, hipStream_t s)
-{
-    if (!receiver_mfma_supported(d, R)) return hipErrorNotSupported;
-    constexpr int WPB = 2, PC = WPB * 64;  // as launch_receiver_mfma
-    const int nchunks = (d.UV + PC - 1) / PC;
-    if (N == 0) return hipSuccess;
-    const int64_t blocks = recv_blocks(N, (int64_t)(R / kRT) * nchunks);
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_gather_probe_mfma<WPB>), dim3((unsigned)blocks), dim3(64 * WPB), 0, s,
-                       d.UV, d.UVs, R, nchunks, N, row_ptr, col, order, SF, sink);
-    return hipGetLastError();
-}
-
 size_t receiver_mfma_ws_elems(const Dims &d, int64_t N, int R, int planes)
 {
     return (size_t)N * R * planes * d.UVs;
@@ -494,58 +375,38 @@ size_t receiver_mfma_ws_elems(const Dims &d, int64_t N, int R, int planes)
 hipError_t launch_receiver_mfma(const Tabs<float> &tb, int64_t N, int R, const int32_t *row_ptr,
                                 const int32_t *col, const int32_t *order, const float *unit,
                                 const float *Rt, const float *Rtg, const float *SF,
-                                const float *SFf, bool sf_chunked, float *S, float *Ta, float *Tb,
-                                hipStream_t s, bool values_only, bool analyse)
+                                const float *SFf, float *S, hipStream_t s)
 {
     if (N == 0) return hipSuccess;
     const Dims &d = tb.d;
     if (!receiver_mfma_supported(d, R)) return hipErrorNotSupported;
     if (SFf && Rtg) return hipErrorNotSupported;
-    if (values_only && SFf && Rtg) return hipErrorInvalidValue;
-    // Waves per workgroup: two (128 grid points); one with two node slots up to lmax 8, whose
-    // six sums leave two waves per SIMD (there more, smaller workgroups measured 2.8% faster
-    // at lmax 6, but 4% slower at lmax 20 and 2.6% slower with one slot).
+    // Waves per workgroup: two (128 grid points); one with two node slots up to lmax 8.
     constexpr int PW = 64;
     const int wpb = SFf && d.lmax <= 8 ? 1 : 2, PC = wpb * PW;
     const int nchunks = (d.UV + PC - 1) / PC;
     const size_t sh = sizeof(float) * wpb * (size_t)recv_lds_floats(d.lmax);
     const int64_t blocks = recv_blocks(N, (int64_t)(R / kRT) * nchunks);
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    static_assert(PW == kSfChunk, "a receiver wave reads one chunk of the chunked layout");
-    const int sf_nc = sf_chunked ? sf_chunks(d) : 0;
-#define CGTP_LAUNCH(LMV, TW, SP, VL)                                                            \
-    hipLaunchKernelGGL((k_receiver_mfma<TW && LMV <= 8 ? 1 : 2, LMV, TW, SP, VL>),            \
-                       dim3((unsigned)blocks),                                                  \
-                       dim3(64 * wpb), sh, s, tb, R, nchunks, N, row_ptr, col, order, unit, Rt, \
-                       Rtg, SF, SFf, sf_nc, S)
+#define CGTP_LAUNCH(LMV, TW, SP)                                                                \
+    hipLaunchKernelGGL((k_receiver_mfma<TW && LMV <= 8 ? 1 : 2, LMV, TW, SP>),                  \
+                       dim3((unsigned)blocks), dim3(64 * wpb), sh, s, tb, R, nchunks, N, row_ptr, \
+                       col, order, unit, Rt, Rtg, SF, SFf, S)
     switch (d.lmax) {
 #define CGTP_CASE(LMV)                                                 \
     case LMV:                                                          \
-        if (values_only) {                                             \
-            if (SFf) CGTP_LAUNCH(LMV, true, false, true);              \
-            else if (Rtg) CGTP_LAUNCH(LMV, false, true, true);         \
-            else CGTP_LAUNCH(LMV, false, false, true);                 \
-        } else if (LMV < kMfmaRecvMinL) {                              \
-            return hipErrorNotSupported;                               \
-        } else if (SFf) {                                              \
-            CGTP_LAUNCH(LMV, true, false, false);                      \
-        } else if (Rtg) {                                              \
-            CGTP_LAUNCH(LMV, false, true, false);                      \
-        } else {                                                       \
-            CGTP_LAUNCH(LMV, false, false, false);                     \
-        }                                                              \
+        if (SFf) CGTP_LAUNCH(LMV, true, false);                        \
+        else if (Rtg) CGTP_LAUNCH(LMV, false, true);                   \
+        else CGTP_LAUNCH(LMV, false, false);                           \
         break;
-        CGTP_CASE(0) CGTP_CASE(1) CGTP_CASE(2) CGTP_CASE(3) CGTP_CASE(4) CGTP_CASE(5) CGTP_CASE(6)
-        CGTP_CASE(7) CGTP_CASE(8) CGTP_CASE(9) CGTP_CASE(10) CGTP_CASE(11) CGTP_CASE(12) CGTP_CASE(13) CGTP_CASE(14)
-        CGTP_CASE(15) CGTP_CASE(16) CGTP_CASE(17) CGTP_CASE(18) CGTP_CASE(19) CGTP_CASE(20)
-        CGTP_CASE(21) CGTP_CASE(22) CGTP_CASE(23) CGTP_CASE(24)
+        CGTP_CASE(7) CGTP_CASE(8) CGTP_CASE(9) CGTP_CASE(10) CGTP_CASE(11) CGTP_CASE(12)
+        CGTP_CASE(13) CGTP_CASE(14) CGTP_CASE(15) CGTP_CASE(16) CGTP_CASE(17) CGTP_CASE(18)
+        CGTP_CASE(19) CGTP_CASE(20) CGTP_CASE(21) CGTP_CASE(22) CGTP_CASE(23) CGTP_CASE(24)
 #undef CGTP_CASE
 #undef CGTP_LAUNCH
     default: return hipErrorNotSupported;
     }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !analyse) return e;
-    return launch_summed_analysis(tb, N, R, S, Ta, Tb, s, values_only ? (SFf ? 2 : 1) : 0);
+    return hipGetLastError();
 }
 
 hipError_t launch_summed_analysis(const Tabs<float> &tb, int64_t N, int R, const float *S,

@@ -1,0 +1,630 @@
+// Message-passing receiver pass reading sender values only (fp32, default grid, rank padded to
+// a multiple of 16), the edge-field synthesis on MFMA.
+//
+// For an edge e the zonal edge field and its t-derivative at grid point p are
+//   a[r][p] = sum_l Rt[e][l][r] P_l(t_p),   g[r][p] = sum_l Rt[e][l][r] P_l'(t_p),
+// t_p = rhat_e . Omega_p (addition theorem; the (2l+1)/(4 pi) weights are folded into Rt): two
+// [16 ranks x L] x [L x 16 points] products per tile. The surface curl takes the
+// moved-derivative form (integration by parts on the sphere): its coefficient is the analysis
+// of S1 = sum_j B_j dA_j/dx against dY/dphi minus that of S2 = sum_j B_j dA_j/dphi against
+// dY/dx, with dA/dx = g dt/dx and dA/dphi = g dt/dphi of the edge field. So a receiver reads the
+// value plane B_j of its senders alone and sums the Gaunt product a B and the pair (S1, S2);
+// S [N][R][3][UVs] (six planes with two node slots) goes to the MFMA analysis in its moved modes.
+//
+// Products on bf16 triples. The fp32 matrix instructions run on the vector ALU's data path:
+// on this chip they do not overlap vector instructions of other waves (16x16x4 fp32 products
+// and FMAs that take 229 and 296 us apart take 510 us together), so a receiver on them paid the
+// sum of its matrix and vector time. The 16x16x32 bf16 instruction is 16 times faster and does
+// overlap (128 and 144 us apart, 192 together). Both operands are therefore held as exact sums
+// of three bf16 parts, x = h + m + l (24 bits of significand, round to nearest each time), and a
+// product is formed from the parts' products hh, hm, mh, mm, hl, lh (up to lmax 7, where there is
+// room, also ml and lm), accumulated in fp32: what is left out is below 2^-24 of the term.
+//
+// Operand layout (lane = 16 g + n, 8 consecutive reduction slots per lane): a slot vector is 8
+// degrees of one part. With one degree group (lmax <= 7) the four lane groups take four part
+// pairs of it, two instructions; with two groups (lmax <= 15) two part pairs of both, three
+// instructions; above, one part pair of up to four groups, six instructions.
+//
+// Sender values come in tiles of 16 ranks x 16 points, 1 KB each in the order a wave reads
+// them: SF [N][R/16][UVs/16][64 lanes][4], lane 16 g + n holding ranks 4 g .. 4 g + 3 of point
+// n (with per-block factors a second such plane follows). One 16-byte load per lane then
+// fetches whole lines; the same bytes as rows [R][UVs], 16 segments of 64 bytes per load, ran
+// at a third of the rate (the loads alone, 10^4 nodes, lmax 6, R = 128, 525,308 edges: 5.56 ms
+// in rows, 1.8 ms in tiles; lmax 20, 5,000 nodes, R = 64: 13.7 and 4.4 ms).
+//
+// A wave owns RT rank tiles x PT point tiles of one receiver and works alone. P_l and P_l' of an
+// edge do not depend on the rank: a lane runs the recurrence at one point for one of 4 / PT
+// edges, splits the values into parts once for all ranks and leaves them in wave-private LDS
+// (no barrier). Sharing them between the waves of a workgroup instead halves that work but left
+// the waves waiting for each other (6.5 ms at 10^4 nodes, lmax 6, R = 128, 525,308 edges).
+// The waves of a workgroup take neighbouring points, so that the edge coefficients they all
+// read meet in L1.
+//
+// Measured (receiver alone, before: fp32 products, values in rows, one wave per 16 ranks and 64
+// points): 10^4 nodes, lmax 6, R = 128, 525,308 edges 6.98 -> 5.58 ms; 5,000 nodes, lmax 20,
+// R = 64, 35.0 -> 27.9 ms; two slots, 5,000 nodes, lmax 6, R = 128, 6.81 -> 4.56 ms; per-block
+// factors, 3,000 nodes, lmax 6, 128 stacked ranks, 3.78 -> 3.06 ms. What bounds it now is the
+// power limit: it needs a third fewer cycles than the fp32 form, but the clock falls from 2.05
+// to 1.75 GHz with matrix cores (31% busy), vector ALU (56%) and gather all running. A single
+// rank tile above lmax 15 pays its recurrences alone and is slower than it was (2.6 -> 3.2 ms,
+// 2,000 nodes, lmax 18, R = 16).
+#include "internal.h"
+
+namespace cgtp {
+
+namespace {
+
+typedef float float4_t __attribute__((ext_vector_type(4)));
+typedef float float2_t __attribute__((ext_vector_type(2)));
+typedef unsigned uint2_t __attribute__((ext_vector_type(2)));
+typedef unsigned uint4_t __attribute__((ext_vector_type(4)));
+typedef __bf16 bf2_t __attribute__((ext_vector_type(2)));
+typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void *base, unsigned bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, (int)bytes,
+                                             0x00020000);
+}
+
+template <typename V>
+__device__ __forceinline__ V bload16(__amdgpu_buffer_rsrc_t rs, unsigned voff, unsigned soff)
+{
+    return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(rs, voff, soff, 0));
+}
+
+// A byte offset past every resource here: loads return 0.
+constexpr unsigned kOut = 0x80000000u;
+// Waves per workgroup (neighbouring points): two, so that few of them lie past the grid; four
+// with two coefficient sets, which share twice the coefficients through L1, one with a single
+// rank tile, whose 64 points are a larger share of the grid (3.05 against 3.14 ms,
+// 3,000 nodes, lmax 6, 128 stacked ranks).
+constexpr int waves_for(bool split, int rt) { return split ? 4 : rt == 1 ? 1 : 2; }
+constexpr int kSplitWaves = 4;  // waves per workgroup that share one wave's edges (ES)
+
+// Wave-private LDS in bytes: 64 (edge, point) pairs, each with the slot vectors of P_l, then of
+// P_l' (8 bf16 each; with one degree group a zero vector after each), and dt/dx and dt/dphi.
+// Layout [edge][P, P'][part][degree group][points][8 bf16], then [edge][2][points].
+constexpr int plane_vecs(int ndg) { return 3 * ndg + (ndg == 1 ? 1 : 0); }
+constexpr int wave_bytes(int ndg) { return 64 * (2 * plane_vecs(ndg) * 16 + 2 * 4); }
+
+// Operand vectors by degree groups. Lane group g of instruction i multiplies a part (0 h, 1 m,
+// 2 l, 3 zero) of A vector av(i) with one of B vector bv(i), of the degree group group(g):
+//   NDG 1: A h m l h with B h h h m, then B l m m 0: hh mh lh hm, hl mm lm
+//   NDG 2: A h h m m with B h h h h, then B m m m m; A h h l l with B l l h h: hh mh, hm mm, hl lh
+//   above: one part pair per instruction: hh hm mh mm hl lh
+template <int NDG>
+struct Slots {
+    static constexpr int NI = NDG == 1 ? 2 : NDG == 2 ? 3 : 6;
+    static constexpr int NA = NDG <= 2 ? NDG : 3, NB = NDG == 1 ? 2 : 3;
+    static constexpr int av(int i) { return NDG == 1 ? 0 : NDG == 2 ? i / 2 : (const int[6]){0, 0, 1, 1, 0, 2}[i]; }
+    static constexpr int bv(int i) { return NDG <= 2 ? i : (const int[6]){0, 1, 0, 1, 2, 0}[i]; }
+    static __device__ int apart(int k, int g)
+    {
+        if (NDG == 1) return g == 3 ? 0 : g;
+        if (NDG == 2) return k == 0 ? g >> 1 : (g >> 1) * 2;
+        return k;
+    }
+    static __device__ int bpart(int k, int g)
+    {
+        if (NDG == 1) return k == 0 ? (g == 3 ? 1 : 0) : (g == 0 ? 2 : g == 3 ? 3 : 1);
+        if (NDG == 2) return k < 2 ? k : 2 - (g >> 1) * 2;
+        return k;
+    }
+    // degree group of lane group g (>= NDG: none)
+    static __device__ int group(int g) { return NDG == 1 ? 0 : NDG == 2 ? g & 1 : g; }
+};
+
+// The three bf16 parts of 8 values (degrees past the last are zero), as slot vectors. The
+// residual x - part is one dot product instruction (exact: the parts cancel leading bits).
+__device__ __forceinline__ void split8(const float (&x)[8], uint4_t (&part)[3])
+{
+    // (-1, 0) and (0, -1), kept from the compiler: as an inline constant the first would be read
+    // as the second. So would a part known at compile time (P_0 = 1).
+    unsigned lob = 0x0000bf80u, hib = 0xbf800000u;
+    asm("" : "+s"(lob), "+s"(hib));
+    const bf2_t lo = __builtin_bit_cast(bf2_t, lob), hi = __builtin_bit_cast(bf2_t, hib);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        float2_t r = {x[2 * k], x[2 * k + 1]};
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            unsigned bits = __builtin_bit_cast(unsigned, __builtin_convertvector(r, bf2_t));
+            asm("" : "+v"(bits));
+            const bf2_t w = __builtin_bit_cast(bf2_t, bits);
+            part[c][k] = bits;
+            if (c < 2) {
+                r[0] = __builtin_amdgcn_fdot2_f32_bf16(w, lo, r[0], false);
+                r[1] = __builtin_amdgcn_fdot2_f32_bf16(w, hi, r[1], false);
+            }
+        }
+    }
+}
+
+// Block order of the receiver: rank group by rank group; inside, each XCD takes a contiguous
+// span of the receiver sequence (as recv_block) and the point chunks of one receiver run back to
+// back, so that the edge coefficients they share stay in its L2.
+__device__ __forceinline__ bool recv_chunk_block(int64_t N, const int32_t *order, int nchunks,
+                                                 int &rg, int64_t &i, int &chunk)
+{
+    const int64_t m = recv_span(N), k = blockIdx.x / kXcds, per = m * nchunks;
+    rg = (int)(k / per);
+    const int64_t rem = k - rg * per, q = rem / nchunks;
+    chunk = (int)(rem - q * nchunks);
+    const int64_t pos = (blockIdx.x % kXcds) * m + q;
+    if (pos >= N) return false;
+    i = order ? (int64_t)order[pos] : pos;
+    return true;
+}
+
+// Wave-scope ordering of LDS accesses (LDS operations of a wave complete in order; the fences
+// keep the compiler from moving accesses across).
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// TWO: the senders carry a second, parity-flipped node slot SFf (same layout as SF); by
+// Table 1 its curl then feeds S_alpha's slot (natural parity) and its Gaunt product S_beta's.
+// SPLIT: per-block factors. The derivative sum g multiplies P' with the curl factors' edge
+// coefficients Rtg and its products take the curl factors' values, plane 1 of SF.
+// Rt, Rtg: edge coefficients in parts, [E][R/16][3 parts][NDG][16 ranks][8 degrees] bf16 (4
+// degrees up to lmax 3).
+// ES: the workgroup's waves (kSplitWaves) take one wave's tiles together, a share of the edges
+// each, and add up their sums in wave order.
+template <int LM, int RT, int PT, bool TWO, bool SPLIT, bool ES>
+__global__ __launch_bounds__(64 * (ES ? kSplitWaves : waves_for(SPLIT, RT)))
+__attribute__((amdgpu_waves_per_eu(2))) void k_receiver_values(Tabs<float> tb, int R, int nchunks, int64_t N,
+                       const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
+                       const int32_t *__restrict__ order, const float *__restrict__ unit,
+                       const void *__restrict__ Rt, const void *__restrict__ Rtg,
+                       const float *__restrict__ SF, const float *__restrict__ SFf,
+                       float *__restrict__ S)
+{
+    constexpr int NDG = rt_groups(LM);
+    // bytes of a stored slot vector, and of a rank tile's
+    constexpr int VB = rt_vec_bytes(LM), TB = 3 * NDG * 16 * VB;
+    using SL = Slots<NDG>;
+    constexpr int PW = 16 * PT, EG = 64 / PW;  // points of a wave, edges per recurrence pass
+    constexpr int PLANE = plane_vecs(NDG) * PW * 16;  // P's or P''s vectors of one edge
+    constexpr int DXS = EG * 2 * PLANE;               // byte offset of dt/dx, dt/dphi
+    const Dims &d = tb.d;
+    const int UV = d.UV, UVs = d.UVs, NT = UVs / 16, RTL = R / 16;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int g = lane >> 4, n = lane & 15;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    char *lds = smem + wave * wave_bytes(NDG);
+
+    int64_t i;
+    int rg, ch;
+    if (!recv_chunk_block(N, order, nchunks, rg, i, ch)) return;  // the whole workgroup
+    const int p0 = (ES ? ch : ch * waves_for(SPLIT, RT) + wave) * PW;  // first point of the wave
+    const int rt0 = rg * RT;                                            // its first rank tile
+    if (p0 >= UV) return;  // waves never wait for each other (ES: the whole workgroup)
+    // its rank tiles; the products of tiles past the last run on zeros
+    const int na = RTL - rt0 < RT ? RTL - rt0 : RT;
+
+    // This lane's recurrence point (points past the grid compute on point 0, never stored).
+    const int hl = lane & (PW - 1), he = lane / PW;
+    const int prc = p0 + hl < UV ? p0 + hl : 0;
+    const int ur = prc / d.V, vr = prc - ur * d.V;
+    const float rx = tb.x[ur], rsx = tb.sx[ur], rxsx = tb.xsx[ur], rcp = tb.cphi[vr],
+                rsp = tb.sphi[vr];
+    // the wave's edges: the receiver's, or (ES) a quarter of them
+    int e0 = row_ptr[i], e1 = row_ptr[i + 1];
+    if (ES) {
+        const int len = e1 - e0, first = e0;
+        e0 = first + (int)((int64_t)len * wave / kSplitWaves);
+        e1 = first + (int)((int64_t)len * (wave + 1) / kSplitWaves);
+    }
+    // the direction of this lane's edge of a pass, loaded a pass ahead
+    float nux = 0.f, nuy = 0.f, nuz = 1.f;
+    auto load_unit = [&](int b) {
+        const float *v = unit + 3 * (int64_t)(b + he < e1 ? b + he : e0);
+        nux = v[0];
+        nuy = v[1];
+        nuz = v[2];
+    };
+    // P_l, P_l' of edges b .. b + EG - 1 at the wave's points, in parts, into LDS
+    auto legendre = [&]() {
+        // renormalised by the hardware reciprocal square root (within 1 ulp)
+        const float inv = __builtin_amdgcn_rsqf(nux * nux + nuy * nuy + nuz * nuz);
+        const float ux = nux * inv, uy = nuy * inv, uz = nuz * inv;
+        // t = rhat . Omega at this lane's point; P_l(t) and P_l'(t) by the Legendre and
+        // derivative recurrences
+        const float h = ux * rcp + uy * rsp;
+        const float t = uz * rx + rsx * h;
+        float *dxs = reinterpret_cast<float *>(lds + DXS) + he * 2 * PW + hl;
+        dxs[0] = uz - rxsx * h;
+        dxs[PW] = rsx * (uy * rcp - ux * rsp);
+        uint4_t *o = reinterpret_cast<uint4_t *>(lds + he * 2 * PLANE) + hl;
+        // P_l = ((2l-1) t P_{l-1} - (l-1) P_{l-2}) / l,  P_l' = l P_{l-1} + t P_{l-1}' (the form
+        // P_{l-2}' + (2l-1) P_{l-1} is one operation shorter and measured less accurate)
+        float p0v = 0.f, p1v = 0.f, d1 = 0.f;  // P_{l-2}, P_{l-1}, P_{l-1}'
+#pragma unroll
+        for (int dg = 0; dg < NDG; ++dg) {
+            float v[8], w[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int l = 8 * dg + k;
+                v[k] = w[k] = 0.f;
+                if (l > LM) continue;
+                float p2 = l == 0 ? 1.f : t;
+                float d2 = l == 0 ? 0.f : 1.f;
+                if (l >= 2) {
+                    const float c1 = (float)(2 * l - 1) / (float)l, c2 = (float)(l - 1) / (float)l;
+                    p2 = c1 * t * p1v - c2 * p0v;
+                    d2 = (float)l * p1v + t * d1;
+                }
+                v[k] = p2;
+                w[k] = d2;
+                p0v = p1v;
+                p1v = p2;
+                d1 = d2;
+            }
+            uint4_t part[3];
+            split8(v, part);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) o[(c * NDG + dg) * PW] = part[c];
+            split8(w, part);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) o[(plane_vecs(NDG) + c * NDG + dg) * PW] = part[c];
+        }
+    };
+
+    // D[row = rank 4 g + j][col = point n]: a lane holds four ranks of one point. sa, sb: the
+    // Gaunt sums into S_alpha, S_beta; (ca1, ca2) the moved curl pair into S_alpha (the flipped
+    // slot's, TWO), (cb1, cb2) into S_beta (the natural slot's).
+    float4_t sa[RT][PT], sb[RT][PT], ca1[RT][PT], ca2[RT][PT], cb1[RT][PT], cb2[RT][PT];
+#pragma unroll
+    for (int a = 0; a < RT; ++a)
+#pragma unroll
+        for (int t = 0; t < PT; ++t)
+            sa[a][t] = sb[a][t] = ca1[a][t] = ca2[a][t] = cb1[a][t] = cb2[a][t] =
+                float4_t{0.f, 0.f, 0.f, 0.f};
+
+    const int64_t jstride = (int64_t)R * UVs;  // sender stride of a value plane
+    const int64_t sfo = ((int64_t)rt0 * NT + p0 / 16) * 256;
+    const float *sfb = SF + sfo;
+    const float *sfx = (TWO ? SFf : SF + N * jstride) + sfo;  // flipped slot, or plane 1
+    // to the end of the wave's last rank tile; a point tile past the row's end reads on into the
+    // next rank tile's values, or 0: its points are past the grid
+    const unsigned sfbytes = (unsigned)(na * NT - p0 / 16) * 1024u;
+    // A operands: slot vectors of the edge's rank tiles; B operands: slot
+    // vectors of P, P' at the wave's points. Lane groups without a degree group take zeros for A
+    // and any (finite) vector for B.
+    unsigned ao[SL::NA], bo[SL::NB];
+    const int dgl = SL::group(g);
+#pragma unroll
+    for (int k = 0; k < SL::NA; ++k)
+        ao[k] = dgl < NDG ? (unsigned)((SL::apart(k, g) * NDG + dgl) * 16 + n) * VB : kOut;
+#pragma unroll
+    for (int k = 0; k < SL::NB; ++k)
+        bo[k] = (unsigned)((SL::bpart(k, g) * NDG + (dgl < NDG ? dgl : 0)) * (PW * 16) + n * 16);
+    const char *rtb = static_cast<const char *>(Rt) + rt0 * TB;
+    const char *rtgb = static_cast<const char *>(Rtg) + (SPLIT ? rt0 * TB : 0);
+
+    // sender indices in batches of 64 edges: lane k holds that of edge k of the batch, read out
+    // with readlane, so no load of an index sits on an edge's critical path (coln: the next 64)
+    int colv = 0, coln = 0;
+    auto load_col = [&](int e) { return e + lane < e1 ? col[e + lane] : 0; };
+    // An edge's values and coefficients are requested one edge ahead, tile by tile, each right
+    // after its registers' last use (past the last edge the last is requested again).
+    float4_t f[RT][PT], x[RT][PT];
+    bf8_t A[RT][SL::NA], Ag[RT][SL::NA];
+    auto load_a = [&](__amdgpu_buffer_rsrc_t rs, int a, bf8_t (&v)[SL::NA]) {
+#pragma unroll
+        for (int k = 0; k < SL::NA; ++k) {
+            if constexpr (VB == 16) {
+                v[k] = bload16<bf8_t>(rs, ao[k], (unsigned)(a * TB));
+            } else {  // half vectors: four degrees
+                const uint2_t w = __builtin_bit_cast(
+                    uint2_t, __builtin_amdgcn_raw_buffer_load_b64(rs, ao[k], (unsigned)(a * TB), 0));
+                v[k] = __builtin_bit_cast(bf8_t, uint4_t{w[0], w[1], 0, 0});
+            }
+        }
+    };
+    auto load_f = [&](__amdgpu_buffer_rsrc_t rs, int a, int t) {
+        return bload16<float4_t>(rs, lane * 16u, (unsigned)(a * NT + t) * 1024u);
+    };
+    struct Next {
+        __amdgpu_buffer_rsrc_t f, x, a, ag;
+    };
+    auto next_edge = [&](int e) {
+        const int ec = e < e1 ? e : e1 - 1;
+        const int k = (ec - e0) & 63;
+        if (k == 0 && e > e0 && e < e1) {
+            colv = coln;
+            coln = load_col(e + 64);
+        }
+        const int64_t j = __builtin_amdgcn_readlane(colv, k);
+        Next r;
+        r.f = rsrc(sfb + j * jstride, sfbytes);
+        r.x = rsrc(sfx + j * jstride, sfbytes);
+        r.a = rsrc(rtb + (int64_t)ec * RTL * TB, (unsigned)(na * TB));
+        r.ag = rsrc(rtgb + (int64_t)ec * RTL * TB, (unsigned)(na * TB));
+        return r;
+    };
+    auto edge = [&](int e, int q) {
+        const Next nx = next_edge(e + 1);
+        const char *u = lds + q * 2 * PLANE;
+        const float *dxs = reinterpret_cast<const float *>(lds + DXS) + q * 2 * PW + n;
+#pragma unroll
+        for (int t = 0; t < PT; ++t) {
+            bf8_t pv[SL::NB], dv[SL::NB];
+#pragma unroll
+            for (int k = 0; k < SL::NB; ++k) {
+                pv[k] = *reinterpret_cast<const bf8_t *>(u + bo[k] + t * 256);
+                dv[k] = *reinterpret_cast<const bf8_t *>(u + PLANE + bo[k] + t * 256);
+            }
+            const float dxt = dxs[16 * t], dpt = dxs[PW + 16 * t];
+#pragma unroll
+            for (int a = 0; a < RT; ++a) {
+                float4_t va = float4_t{0.f, 0.f, 0.f, 0.f}, gg = va;
+                // the small part products first
+#pragma unroll
+                for (int k = SL::NI - 1; k >= 0; --k) {
+                    va = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[a][SL::av(k)], pv[SL::bv(k)],
+                                                                 va, 0, 0, 0);
+                    gg = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        SPLIT ? Ag[a][SL::av(k)] : A[a][SL::av(k)], dv[SL::bv(k)], gg, 0, 0, 0);
+                }
+                if (t == PT - 1) {
+                    load_a(nx.a, a, A[a]);
+                    if (SPLIT) load_a(nx.ag, a, Ag[a]);
+                }
+#pragma unroll
+                for (int jj = 0; jj < 4; ++jj) {
+                    const float fv = f[a][t][jj], xv = (TWO || SPLIT) ? x[a][t][jj] : fv;
+                    sa[a][t][jj] += va[jj] * fv;
+                    const float gf = gg[jj] * (SPLIT ? xv : fv);
+                    cb1[a][t][jj] += dxt * gf;
+                    cb2[a][t][jj] += dpt * gf;
+                    if (TWO) {
+                        sb[a][t][jj] += va[jj] * xv;
+                        const float gh = gg[jj] * xv;
+                        ca1[a][t][jj] += dxt * gh;
+                        ca2[a][t][jj] += dpt * gh;
+                    }
+                }
+                f[a][t] = load_f(nx.f, a, t);
+                if (TWO || SPLIT) x[a][t] = load_f(nx.x, a, t);
+            }
+        }
+    };
+
+    if (e0 < e1) {
+        load_unit(e0);
+        colv = load_col(e0);
+        coln = load_col(e0 + 64);
+        {
+            const Next nx = next_edge(e0);
+#pragma unroll
+            for (int a = 0; a < RT; ++a) {
+                load_a(nx.a, a, A[a]);
+                if (SPLIT) load_a(nx.ag, a, Ag[a]);
+#pragma unroll
+                for (int t = 0; t < PT; ++t) {
+                    f[a][t] = load_f(nx.f, a, t);
+                    if (TWO || SPLIT) x[a][t] = load_f(nx.x, a, t);
+                }
+            }
+        }
+        if (NDG == 1) {  // the zero vectors
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+                *reinterpret_cast<uint4_t *>(lds + (he * 2 + k) * PLANE + (3 * PW + hl) * 16) =
+                    uint4_t{0, 0, 0, 0};
+        }
+        for (int b = e0; b < e1; b += EG) {
+            wave_sync();  // the pass before is read
+            legendre();
+            load_unit(b + EG);
+            wave_sync();
+            const int be = e1 - b < EG ? e1 - b : EG;
+            for (int q = 0; q < be; ++q) edge(b + q, q);
+        }
+    }
+    // S[i][r][plane][p]: planes (sa, cb1, cb2), with two slots (sa, ca1, ca2, sb, cb1, cb2)
+    constexpr int NF = TWO ? 6 : 3;
+    if constexpr (ES) {
+        // every wave's sums of one plane in LDS, [wave][tile][64 lanes][4]; wave 0 adds them up
+        float4_t *sum = reinterpret_cast<float4_t *>(smem);
+        auto reduce = [&](float4_t (&v)[RT][PT]) {
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < RT * PT; ++k)
+                sum[(wave * RT * PT + k) * 64 + lane] = v[k / PT][k % PT];
+            __syncthreads();
+            if (wave == 0) {
+#pragma unroll
+                for (int k = 0; k < RT * PT; ++k)
+#pragma unroll
+                    for (int w = 1; w < kSplitWaves; ++w)
+                        v[k / PT][k % PT] += sum[(w * RT * PT + k) * 64 + lane];
+            }
+        };
+        reduce(sa);
+        reduce(cb1);
+        reduce(cb2);
+        if (TWO) {
+            reduce(sb);
+            reduce(ca1);
+            reduce(ca2);
+        }
+        if (wave != 0) return;
+    }
+#pragma unroll
+    for (int t = 0; t < PT; ++t) {
+        const int p = p0 + 16 * t + n;
+        if (p >= UV) continue;
+#pragma unroll
+        for (int a = 0; a < RT; ++a) {
+            if (a >= na) continue;
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj) {
+                float *o = S + (i * R + 16 * (rt0 + a) + 4 * g + jj) * NF * (int64_t)UVs + p;
+                o[0] = sa[a][t][jj];
+                o[UVs] = TWO ? ca1[a][t][jj] : cb1[a][t][jj];
+                o[2 * UVs] = TWO ? ca2[a][t][jj] : cb2[a][t][jj];
+                if (TWO) {
+                    o[3 * UVs] = sb[a][t][jj];
+                    o[4 * UVs] = cb1[a][t][jj];
+                    o[5 * UVs] = cb2[a][t][jj];
+                }
+            }
+        }
+    }
+}
+
+// Read-pattern ceiling of k_receiver_values: the same blocks in the same order, the same
+// wave-uniform sender index per edge and the same 16-byte loads of the value tiles, with
+// nothing computed from them but a running sum; sink receives a value only if that sum equals
+// a constant no finite input sums to by chance, which keeps every load live.
+template <int RT, int PT>
+__global__ __launch_bounds__(64 * waves_for(false, RT)) void k_gather_probe_values(
+    int UV, int UVs, int R, int nchunks, int64_t N, const int32_t *__restrict__ row_ptr,
+    const int32_t *__restrict__ col, const int32_t *__restrict__ order,
+    const float *__restrict__ SF, float *__restrict__ sink)
+{
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int NT = UVs / 16;
+    int64_t i;
+    int rg, ch;
+    if (!recv_chunk_block(N, order, nchunks, rg, i, ch)) return;
+    const int p0 = (ch * waves_for(false, RT) + wave) * 16 * PT;
+    if (p0 >= UV) return;
+    const int na = R / 16 - rg * RT < RT ? R / 16 - rg * RT : RT;
+    const float *sfb = SF + ((int64_t)rg * RT * NT + p0 / 16) * 256;
+    const unsigned bytes = (unsigned)(na * NT - p0 / 16) * 1024u;
+    const int64_t jstride = (int64_t)R * UVs;
+    float4_t acc = float4_t{0.f, 0.f, 0.f, 0.f};
+    const int e0 = row_ptr[i], e1 = row_ptr[i + 1];
+    for (int e = e0; e < e1; ++e) {
+        const int64_t j = __builtin_amdgcn_readfirstlane(col[e]);
+        const __amdgpu_buffer_rsrc_t rs = rsrc(sfb + j * jstride, bytes);
+#pragma unroll
+        for (int a = 0; a < RT; ++a)
+#pragma unroll
+            for (int t = 0; t < PT; ++t)
+                if (a < na) acc += bload16<float4_t>(rs, lane * 16u, (unsigned)(a * NT + t) * 1024u);
+    }
+    const float sum = acc[0] + acc[1] + acc[2] + acc[3];
+    if (sum == -1.2345678e30f) sink[0] = sum;
+}
+
+// Rank tiles of a wave: as many as R has up to four (they share a recurrence). A wave holds
+// eight tiles (rank x point), whose sums fill half of the registers of two waves per SIMD; four,
+// two by two, with two node slots (twice the sums) or two coefficient sets (1,024-element waves of
+// four rank tiles took 4.6 -> 5.4 ms with two slots, 5,000 nodes, lmax 6, R = 128).
+int rank_tiles(int R, bool half)
+{
+    const int tiles = R / 16;
+    return tiles == 1 ? 1 : tiles == 2 || half ? 2 : 4;
+}
+
+// Tiles (rank x point) of all receivers below which a receiver's edges are split over the waves
+// of a workgroup: with fewer the waves, eight tiles each, would not fill the 1024 SIMDs twice.
+constexpr int64_t kSplitTiles = 8 * 2048;
+
+template <int LM, int RT, int PT, bool TWO, bool SPLIT, bool ES>
+hipError_t receiver_rt(const Tabs<float> &tb, int64_t N, int R, const int32_t *row_ptr,
+                       const int32_t *col, const int32_t *order, const float *unit,
+                       const void *Rt, const void *Rtg, const float *SF, const float *SFf,
+                       float *S, hipStream_t s)
+{
+    const Dims &d = tb.d;
+    const int groups = (R / 16 + RT - 1) / RT, waves = ES ? kSplitWaves : waves_for(SPLIT, RT);
+    const int chunk = 16 * PT * (ES ? 1 : waves), nchunks = (d.UV + chunk - 1) / chunk;
+    const int64_t blocks = recv_blocks(N, (int64_t)groups * nchunks);
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    size_t lds = (size_t)waves * wave_bytes(rt_groups(LM));
+    const size_t sums = (size_t)kSplitWaves * RT * PT * 1024;
+    if (ES && lds < sums) lds = sums;
+    if (lds > (size_t)d.lds_max) return hipErrorNotSupported;
+    hipLaunchKernelGGL((k_receiver_values<LM, RT, PT, TWO, SPLIT, ES>), dim3((unsigned)blocks),
+                       dim3(64 * waves), lds, s, tb, R, nchunks, N, row_ptr, col, order, unit, Rt,
+                       Rtg, SF, SFf, S);
+    return hipGetLastError();
+}
+
+template <int LM>
+hipError_t receiver_lm(const Tabs<float> &tb, int64_t N, int R, const int32_t *row_ptr,
+                       const int32_t *col, const int32_t *order, const float *unit,
+                       const void *Rt, const void *Rtg, const float *SF, const float *SFf,
+                       float *S, hipStream_t s)
+{
+    const int rt = rank_tiles(R, SFf || Rtg);
+#define CGTP_LAUNCH(RTV, PTV, TW, SP, ESV)                                                       \
+    return receiver_rt<LM, RTV, PTV, TW, SP, ESV>(tb, N, R, row_ptr, col, order, unit, Rt, Rtg,  \
+                                                  SF, SFf, S, s)
+    if (N * (R / 16) * (tb.d.UVs / 16) < kSplitTiles) {
+        if (SFf) CGTP_LAUNCH(2, 2, true, false, true);
+        if (Rtg) CGTP_LAUNCH(2, 2, false, true, true);
+        CGTP_LAUNCH(2, 2, false, false, true);
+    }
+    if (SFf) {
+        if (rt == 1) CGTP_LAUNCH(1, 4, true, false, false);
+        CGTP_LAUNCH(2, 2, true, false, false);
+    }
+    if (Rtg) {
+        if (rt == 1) CGTP_LAUNCH(1, 4, false, true, false);
+        CGTP_LAUNCH(2, 2, false, true, false);
+    }
+    if (rt == 1) CGTP_LAUNCH(1, 4, false, false, false);
+    if (rt == 2) CGTP_LAUNCH(2, 4, false, false, false);
+    CGTP_LAUNCH(4, 2, false, false, false);
+#undef CGTP_LAUNCH
+}
+
+}  // namespace
+
+hipError_t launch_receiver_values(const Tabs<float> &tb, int64_t N, int R, const int32_t *row_ptr,
+                                  const int32_t *col, const int32_t *order, const float *unit,
+                                  const void *Rt, const void *Rtg, const float *SF,
+                                  const float *SFf, float *S, hipStream_t s)
+{
+    if (N == 0) return hipSuccess;
+    if (R % 16 != 0 || !sender_mfma_supported(tb.d)) return hipErrorNotSupported;
+    if (SFf && Rtg) return hipErrorInvalidValue;
+    switch (tb.d.lmax) {
+#define CGTP_CASE(LMV) \
+    case LMV: return receiver_lm<LMV>(tb, N, R, row_ptr, col, order, unit, Rt, Rtg, SF, SFf, S, s);
+        CGTP_CASE(0) CGTP_CASE(1) CGTP_CASE(2) CGTP_CASE(3) CGTP_CASE(4) CGTP_CASE(5) CGTP_CASE(6)
+        CGTP_CASE(7) CGTP_CASE(8) CGTP_CASE(9) CGTP_CASE(10) CGTP_CASE(11) CGTP_CASE(12)
+        CGTP_CASE(13) CGTP_CASE(14) CGTP_CASE(15) CGTP_CASE(16) CGTP_CASE(17) CGTP_CASE(18)
+        CGTP_CASE(19) CGTP_CASE(20) CGTP_CASE(21) CGTP_CASE(22) CGTP_CASE(23) CGTP_CASE(24)
+#undef CGTP_CASE
+    default: return hipErrorNotSupported;
+    }
+}
+
+hipError_t launch_gather_probe_values(const Dims &d, int64_t N, int R, const int32_t *row_ptr,
+                                      const int32_t *col, const int32_t *order, const float *SF,
+                                      float *sink, hipStream_t s)
+{
+    if (R % 16 != 0) return hipErrorNotSupported;
+    if (N == 0) return hipSuccess;
+#define CGTP_LAUNCH(RTV, PTV)                                                                    \
+    {                                                                                            \
+        constexpr int waves = waves_for(false, RTV);                                             \
+        const int groups = (R / 16 + RTV - 1) / RTV, chunk = 16 * PTV * waves;                   \
+        const int nchunks = (d.UV + chunk - 1) / chunk;                                          \
+        const int64_t blocks = recv_blocks(N, (int64_t)groups * nchunks);                        \
+        if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;                                  \
+        hipLaunchKernelGGL((k_gather_probe_values<RTV, PTV>), dim3((unsigned)blocks),            \
+                           dim3(64 * waves), 0, s, d.UV, d.UVs, R, nchunks, N, row_ptr, col,    \
+                           order, SF, sink);                                                     \
+    }
+    switch (rank_tiles(R, false)) {
+    case 4: CGTP_LAUNCH(4, 2) break;
+    case 2: CGTP_LAUNCH(2, 4) break;
+    default: CGTP_LAUNCH(1, 4) break;
+    }
+#undef CGTP_LAUNCH
+    return hipGetLastError();
+}
+
+}  // namespace cgtp

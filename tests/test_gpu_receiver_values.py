@@ -1,0 +1,78 @@
+"""The values-only message-passing receiver against the fp64 oracle at the edges of its tiling:
+degree groups of 4, 8, 16 and 24 slots (lmax 3/4, 7/8, 15/16, 24), ranks padded to 16 and odd
+numbers of rank tiles, the form that splits a receiver's edges over waves (small problems) and
+the one that does not, each with one node slot, two slots and per-block factors. Tolerance: the
+fp32 bar of the other parity tests (2e-5 of the largest output)."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2605_15073_amd import inputs
+from tests.gpu_util import MP_KEYS, TOL_F32, rel_err, run_mp, sample_rows, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def cg():
+    import torch
+
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2605_15073_amd as lib
+
+    lib.load_library()
+    return lib
+
+
+def _tiles(n, lmax, R):
+    """Rank tiles x point tiles of all receivers: below 16384 the edges are split over waves."""
+    uv = ((3 * lmax + 3) // 2) * (3 * lmax + 1)
+    return n * ((R + 15) // 16) * ((uv + 31) // 32 * 2)
+
+
+# (lmax, ranks, nodes): the first five split the edges, the others do not
+SHAPES = [(0, 16, 60), (3, 9, 60), (7, 40, 40), (15, 16, 20), (24, 24, 20),
+          (3, 16, 4200), (4, 100, 1100), (8, 48, 400), (16, 16, 300), (16, 72, 80)]
+
+
+@pytest.mark.parametrize("slots", ["one", "two", "blocks"])
+@pytest.mark.parametrize("lmax,R,n", SHAPES)
+def test_receiver_values_tiles(cg, lmax, R, n, slots):
+    split = _tiles(n, lmax, R) < 16384
+    assert split == (SHAPES.index((lmax, R, n)) < 5)
+    C, r_cut = 5, 2.6
+    rows = sample_rows(n, 10 if lmax < 15 else 3, seed=lmax)
+    if slots == "blocks":
+        d = inputs.general_mp_inputs(n, lmax, C, R, seed=300 + lmax, flip=True, r_cut=r_cut)
+        plan = cg.plan_create(lmax, C, R)
+        t = to_dev(d, MP_KEYS + ("node_flip",))
+        got = cg.message_pass_general(plan, *(t[k] for k in MP_KEYS), node_flip=t["node_flip"])
+    else:
+        d = inputs.mp_inputs(n, lmax, C, R, seed=300 + lmax, r_cut=r_cut, distinct_out=True,
+                             two_slot=slots == "two")
+        plan = cg.plan_create(lmax, C, R)
+        t = to_dev(d, MP_KEYS)
+        kw = {}
+        if slots == "two":
+            kw["node_flip"] = to_dev(d, ("node_flip",))["node_flip"]
+        got = run_mp(cg, plan, t, **kw)
+    ref = oracle.message_pass(lmax, *(d[k] for k in MP_KEYS), receivers=rows,
+                              node_flip=d.get("node_flip"))
+    for a, b in zip(got, ref):
+        assert rel_err(a[rows], b) <= TOL_F32
+
+
+def test_receiver_without_edges_among_others(cg):
+    """Receivers with no edges give zeros in both forms; the others are unchanged."""
+    for n, lmax, R in ((40, 5, 32), (900, 5, 64)):
+        d = inputs.mp_inputs(n, lmax, 4, R, seed=77, r_cut=1.2, distinct_out=True)
+        assert (np.diff(d["row_ptr"]) == 0).any() and d["n_edges"] > 0
+        plan = cg.plan_create(lmax, 4, R)
+        got = run_mp(cg, plan, to_dev(d, MP_KEYS))
+        ref = oracle.message_pass(lmax, *(d[k] for k in MP_KEYS))
+        empty = np.diff(d["row_ptr"]) == 0
+        for a, b in zip(got, ref):
+            assert rel_err(a, b) <= TOL_F32
+            assert float(a[np.where(empty)[0]].abs().max()) == 0.0
