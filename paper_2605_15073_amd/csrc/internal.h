@@ -59,8 +59,12 @@ struct Tabs {
     const T *wdpt;  // [P][Ut] wq[u] * dp transposed
     const T *yc;    // [P] sqrt((2l+1)(l^2-m^2)/(2l-1)): (1-x^2) dPt_l^m/dx
                     //     = yc Pt_{l-1}^m - l x Pt_l^m
-    const T *qd;    // [V][M] the phi-derivative weights of q: column LM + k holds k q[v][LM + k],
-                    // column LM - k holds -k q[v][LM - k] (k >= 1), column LM zero
+    // Azimuths of the folded on-site kernels: V4 = 4 Q >= V points phi_v = 2 pi (v + 1/2) / V4,
+    // as exact as the grid's own, of which the first Q give the others by reflection
+    const T *qf;    // [Q][M] real Fourier factors at phi_v, v < Q (columns as q)
+    const T *qdf;   // [Q][M] their phi-derivative weights: column LM + k holds k qf[v][LM + k],
+                    // column LM - k holds -k qf[v][LM - k] (k >= 1), column LM zero
+    const T *wpf;   // [P][Ut] w_u (2 pi / V4) * p transposed
     const T *ysyn;  // [KP][3 UVs] for lmax <= kDenseSynthMaxL (else empty): row k = (l, m),
                     // KP = K rounded up to 4 (rows past K zero); column f UVs + u V + v holds
                     // Y_k (f = 0), dY_k/dx (f = 1) and dY_k/dphi (f = 2) at grid point (u, v),
@@ -72,6 +76,8 @@ struct Tabs {
 // Degrees up to which the plan builds the dense synthesis table ysyn (the sender fields of
 // a row are then one product of its coefficients with that table).
 constexpr int kDenseSynthMaxL = 6;
+
+inline int fold_quads(const Dims &d) { return (d.V + 3) / 4; }  // Q
 
 // Number of T elements of each table region, in the order of Tabs.
 size_t table_elems(const Dims &d);
@@ -163,7 +169,8 @@ hipError_t launch_onsite_grid(const Tabs<T> &tb, int64_t B, int R, const T *HA, 
 // hipErrorNotSupported above that.
 // HAc, HBc: NULL, or the curl factors' contractions (then HA, HB are the Gaunt factors': the
 // product takes the values of HA, HB and the curl the derivative fields of HAc, HBc).
-constexpr int kOnsiteFoldedMaxL = 14;
+constexpr int kOnsiteFoldedMaxL = 20;
+constexpr int kOnsiteSplitMaxL = 14;  // the form with HAc, HBc
 hipError_t launch_onsite_folded(const Tabs<float> &tb, int64_t B, int R, const float *HA,
                                 const float *HB, float *Ta, float *Tb, hipStream_t s,
                                 const float *HAc = nullptr, const float *HBc = nullptr);
@@ -282,7 +289,7 @@ hipError_t launch_analysis_mfma(const Tabs<float> &tb, int64_t B, int R, const f
 // fp32 on-site grid stage on MFMA (fourier_mfma.hip), default grid only: the same
 // contract as launch_onsite_grid. Used from kOnsiteMfmaMinL up; below it the
 // register-resident folded kernel is faster.
-constexpr int kOnsiteMfmaMinL = 15;
+constexpr int kOnsiteMfmaMinL = 21;
 hipError_t launch_onsite_mfma(const Tabs<float> &tb, int64_t B, int R, const float *HA,
                               const float *HB, float *Ta, float *Tb, hipStream_t s);
 

@@ -168,11 +168,13 @@ static void region_sizes(const Dims &d, size_t *n)
     n[17] = (size_t)d.P * ut;   // wpt
     n[18] = d.P;                // yc
     n[19] = d.lmax <= kDenseSynthMaxL ? (size_t)(d.K + 3) / 4 * 4 * 3 * d.UVs : 0;  // ysyn
-    n[20] = (size_t)d.V * d.M;  // qd
+    n[20] = (size_t)fold_quads(d) * d.M;  // qf
     n[21] = (size_t)d.P * ut;   // wdpt
+    n[22] = (size_t)fold_quads(d) * d.M;  // qdf
+    n[23] = (size_t)d.P * ut;   // wpf
 }
 
-static const int kRegions = 22;
+static const int kRegions = 24;
 
 static size_t round_up(size_t n) { return (n + 63) & ~(size_t)63; }  // 512 B for fp64
 
@@ -239,13 +241,24 @@ void fill_tables(const Dims &d, double *h)
                 h[off[13] + idx] = 0.0;
             }
         }
-    // phi-derivative weights of the Fourier factors (real basis: d/dphi maps cos(k phi) to
-    // -k sin(k phi) and sin(k phi) to k cos(k phi))
-    for (int v = 0; v < d.V; ++v)
+    // the folded kernels' azimuths and quadrature weights, and the phi-derivative weights of
+    // their Fourier factors (real basis: d/dphi maps cos(k phi) to -k sin(k phi) and sin(k phi)
+    // to k cos(k phi))
+    const int quads = fold_quads(d);
+    for (int v = 0; v < quads; ++v) {
+        const double ph = 2.0 * kPi * (v + 0.5) / (4.0 * quads);
+        double *qv = h + off[20] + (size_t)v * d.M + d.lmax;
+        double *dv = h + off[22] + (size_t)v * d.M + d.lmax;
+        qv[0] = 1.0;
         for (int k = 1; k <= d.lmax; ++k) {
-            h[off[20] + (size_t)v * d.M + d.lmax + k] = k * h[off[6] + (size_t)v * d.M + d.lmax + k];
-            h[off[20] + (size_t)v * d.M + d.lmax - k] = -k * h[off[6] + (size_t)v * d.M + d.lmax - k];
+            qv[k] = std::sqrt(2.0) * std::cos(k * ph);
+            qv[-k] = std::sqrt(2.0) * std::sin(k * ph);
+            dv[k] = k * qv[k];
+            dv[-k] = -k * qv[-k];
         }
+    }
+    for (size_t i = 0; i < (size_t)d.P * ut; ++i)
+        h[off[23] + i] = h[off[17] + i] * d.V / (4.0 * quads);
     // Dense synthesis table: with k = l^2 + l + m and the real basis Y_k = Pt_l^|m|(x) q_m(phi),
     // d/dphi maps q_m to -m q_{-m} (cos(m phi) -> -m sin(m phi), sin(|m| phi) -> |m| cos(|m| phi)).
     if (n[19]) {
@@ -304,8 +317,10 @@ Tabs<T> bind_tables(const Dims &d, const void *dev)
     tb.wpt = ptr[17];
     tb.yc = ptr[18];
     tb.ysyn = ptr[19];
-    tb.qd = ptr[20];
+    tb.qf = ptr[20];
     tb.wdpt = ptr[21];
+    tb.qdf = ptr[22];
+    tb.wpf = ptr[23];
     tb.d = d;
     return tb;
 }

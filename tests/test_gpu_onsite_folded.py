@@ -1,0 +1,55 @@
+"""The folded on-site kernels against the fp64 oracle over their degrees: every register and LDS
+shape (lmax 0 to 20; 21 takes the matrix-core kernel), rank blocks with remainders, and grids off
+the default one, whose Gauss-Legendre rows are not held in registers. fp32 bar of the other parity
+tests (2e-5 of the largest output)."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2605_15073_amd import inputs
+from tests.gpu_util import ONSITE_KEYS, TOL_F32, rel_err, run_onsite, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def cg():
+    import torch
+
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2605_15073_amd as lib
+
+    lib.load_library()
+    return lib
+
+
+@pytest.mark.parametrize("grid", ["default", "finer"])
+@pytest.mark.parametrize("lmax,R", [(0, 3), (1, 70), (2, 8), (3, 43), (7, 22), (8, 20), (10, 17),
+                                    (11, 15), (13, 13), (15, 12), (16, 11), (17, 1), (18, 10),
+                                    (19, 9), (20, 9), (21, 3)])
+def test_folded_onsite(cg, lmax, R, grid):
+    d = inputs.onsite_inputs(3, lmax, 4, R, seed=500 + lmax, per_degree=True, distinct_out=True)
+    kw = {} if grid == "default" else dict(n_theta=(3 * lmax + 3) // 2 + 5, n_phi=3 * lmax + 4)
+    plan = cg.plan_create(lmax, 4, R, **kw)
+    got = run_onsite(cg, plan, to_dev(d, ONSITE_KEYS))
+    ref = oracle.onsite(lmax, d["A"], d["B"], d["U_A"], d["U_B"], d["U_out_even"], d["U_out_odd"])
+    for a, b in zip(got, ref):
+        assert rel_err(a, b) <= TOL_F32 or np.abs(b).max() == 0.0
+
+
+@pytest.mark.parametrize("lmax,nu,extra", [(0, 2, 0), (3, 2, 0), (5, 3, 0), (9, 4, 0), (10, 4, 3),
+                                           (4, 3, 6)])
+def test_folded_nbody(cg, lmax, nu, extra):
+    R = 11
+    d = inputs.nbody_inputs(3, lmax, 4, R, seed=600 + lmax, nu=nu, self_coupled=False)
+    nt, nph = cg.nbody_grid(lmax, nu)
+    plan = cg.plan_create(lmax, 4, R, n_theta=nt + extra, n_phi=nph + extra)
+    dev = to_dev({f"x{i}": x for i, x in enumerate(d["X"])} | {f"u{i}": u for i, u in
+                 enumerate(d["U"])} | {"o": d["U_out"]},
+                 [f"x{i}" for i in range(nu)] + [f"u{i}" for i in range(nu)] + ["o"])
+    got = cg.onsite_nbody(plan, [dev[f"x{i}"] for i in range(nu)],
+                          [dev[f"u{i}"] for i in range(nu)], dev["o"])
+    ref = oracle.nbody(lmax, d["X"], d["U"], d["U_out"])
+    assert rel_err(got, ref) <= TOL_F32
