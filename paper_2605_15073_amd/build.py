@@ -11,7 +11,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libcgtp.so")
-SOURCES = ["plan.cpp", "tables.cpp", "order.cpp", "contract.hip", "kernels.hip", "onsite.hip", "receiver_mfma.hip",
+SOURCES = ["plan.cpp", "tables.cpp", "order.cpp", "contract.hip", "contract_rows.hip", "kernels.hip", "onsite.hip", "receiver_mfma.hip",
            "receiver_values.hip", "folded.hip",
            "fourier_mfma.hip", "noalloc.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

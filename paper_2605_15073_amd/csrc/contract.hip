@@ -13,6 +13,7 @@
 // run back to back over all degrees, so the group's input lines are reused from L2. A
 // group of 64 nodes has 64(2l+1) columns of degree l, a whole number of 64-wide tiles,
 // so no tile straddles two degrees and only the last group has a ragged edge.
+// Larger problems go to contract_rows.hip in whole rows.
 // k_contract_kdeg: the case where k is the degree itself (the edge side).
 // fp64 path: one thread per output (verification build).
 #include "internal.h"
@@ -433,6 +434,9 @@ hipError_t launch_contract<float>(int64_t B, int Cin, int Cout, int K, bool kdeg
                            accumulate, nullptr, 0, 0, 0);
         return hipGetLastError();
     }
+    if (!scale && contract_rows_takes(B, Cin, Cout, K, w_sl, w_si, w_so, x_sb))
+        return launch_contract_rows(B, Cin, Cout, K, W, w_sl, w_si, w_so, X, x_sb, Y, y_sb, y_so,
+                                    y_sk, accumulate, nullptr, Pair2{}, s);
     const int64_t groups = (B + kTile - 1) / kTile;
     const int tiles_per_group = K;  // sum over degrees of the (2l+1) tiles of 64 columns
     // 128 outputs per block once there are that many: each X slice is staged once for them
@@ -491,6 +495,9 @@ hipError_t launch_contract_gather(int64_t B, int Cout, int K, const float *W, in
     if (nsrc > kMaxGather || xg.rows <= 0 || xg.rows % kCs != 0) return hipErrorNotSupported;
     const int Cin = nsrc * xg.rows;
     if (x_sb < (int64_t)xg.rows * K) return hipErrorInvalidValue;
+    if (contract_rows_takes(B, Cin, Cout, K, w_sl, w_si, w_so, x_sb))
+        return launch_contract_rows(B, Cin, Cout, K, W, w_sl, w_si, w_so, nullptr, x_sb, Y, y_sb,
+                                    y_so, y_sk, false, &xg, Pair2{}, s);
     const int64_t groups = (B + kTile - 1) / kTile;
     const bool wide = Cout >= 128;
     const int otiles = (Cout + (wide ? 128 : kTile) - 1) / (wide ? 128 : kTile);
@@ -518,6 +525,9 @@ hipError_t launch_contract_pair(int64_t B, int Cin, int Cout, int K, const float
 {
     if (B == 0 || Cout == 0 || K == 0) return hipSuccess;
     if (x_sb < (int64_t)Cin * K) return hipErrorInvalidValue;
+    if (contract_rows_takes(B, Cin, Cout, K, w_sl, w_si, w_so, x_sb))
+        return launch_contract_rows(B, Cin, Cout, K, W0, w_sl, w_si, w_so, X0, x_sb, Y0, y_sb,
+                                    y_so, y_sk, false, nullptr, Pair2{W1, X1, Y1, 0}, s);
     const int64_t groups = (B + kTile - 1) / kTile;
     const bool wide = Cout >= 128;
     const int otiles = (Cout + (wide ? 128 : kTile) - 1) / (wide ? 128 : kTile);

@@ -151,6 +151,29 @@ hipError_t launch_contract_pair(int64_t B, int Cin, int Cout, int K, const float
                                 float *Y1, int64_t y_sb, int64_t y_so, int64_t y_sk,
                                 hipStream_t s);
 
+// The same contractions (kdeg false, no scale) in whole rows on bf16 triples
+// (contract_rows.hip), where contract_rows_takes says so. The rule looks at one problem's sizes
+// only, so that paired and single launches agree. xg: gathered input rows as
+// launch_contract_gather (X unused), or null; second.W: a second problem of the same sizes, or null.
+// Below 16 coefficients (one workgroup's share of k) most of a workgroup would idle; below
+// kRowsMinBlocks workgroups (one per compute unit) k_contract_mfma splits the work more finely
+// (300 nodes, lmax 3, 32 ranks: 80 workgroups against 19). At 256 workgroups a problem the
+// on-site call of 2,048 nodes, lmax 4, 64/64 takes 74 us here and 85 us there.
+constexpr int64_t kRowsMinBlocks = 256;
+inline int64_t contract_rows_w_bytes(int Cin, int Cout, int K, int64_t w_sl, int64_t w_si,
+                                     int64_t w_so)
+{
+    int L = 1;
+    while (L * L < K) ++L;
+    return 4 * ((L - 1) * w_sl + (Cin - 1) * w_si + (Cout - 1) * w_so + 1);
+}
+bool contract_rows_takes(int64_t B, int Cin, int Cout, int K, int64_t w_sl, int64_t w_si,
+                         int64_t w_so, int64_t x_sb);
+hipError_t launch_contract_rows(int64_t B, int Cin, int Cout, int K, const float *W, int64_t w_sl,
+                                int64_t w_si, int64_t w_so, const float *X, int64_t x_sb, float *Y,
+                                int64_t y_sb, int64_t y_so, int64_t y_sk, bool accumulate,
+                                const XGather *xg, Pair2 second, hipStream_t s);
+
 // Node-side synthesis of the three grid fields (A, dA/dx, dA/dphi) of H[b][r][K]:
 // SF[b][r][3][UVs] (Eqs. struct-F, struct-tildeA plus the derivative passes). Only the
 // fields whose bit is set in planes (1: A, 2: dA/dx, 4: dA/dphi) are written; bit 8 writes A
