@@ -49,6 +49,7 @@
 // rank tile above lmax 15 pays its recurrences alone and is slower than it was (2.6 -> 3.2 ms,
 // 2,000 nodes, lmax 18, R = 16).
 #include "internal.h"
+#include "receiver_tiles.h"
 
 namespace cgtp {
 
@@ -174,9 +175,11 @@ __device__ __forceinline__ void wave_sync()
 // degrees up to lmax 3).
 // ES: the workgroup's waves (kSplitWaves) take one wave's tiles together, a share of the edges
 // each, and add up their sums in wave order.
-template <int LM, int RT, int PT, bool TWO, bool SPLIT, bool ES>
+// rt_first: the first rank tile of the launch. PART: the last wave may have fewer than RT rank
+// tiles and skips the others; without it every wave has RT.
+template <int LM, int RT, int PT, bool TWO, bool SPLIT, bool ES, bool PART>
 __global__ __launch_bounds__(64 * (ES ? kSplitWaves : waves_for(SPLIT, RT)))
-__attribute__((amdgpu_waves_per_eu(2))) void k_receiver_values(Tabs<float> tb, int R, int nchunks, int64_t N,
+__attribute__((amdgpu_waves_per_eu(2))) void k_receiver_values(Tabs<float> tb, int R, int rt_first, int nchunks, int64_t N,
                        const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
                        const int32_t *__restrict__ order, const float *__restrict__ unit,
                        const void *__restrict__ Rt, const void *__restrict__ Rtg,
@@ -201,10 +204,10 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_receiver_values(Tabs<float> tb, i
     int rg, ch;
     if (!recv_chunk_block(N, order, nchunks, rg, i, ch)) return;  // the whole workgroup
     const int p0 = (ES ? ch : ch * waves_for(SPLIT, RT) + wave) * PW;  // first point of the wave
-    const int rt0 = rg * RT;                                            // its first rank tile
+    const int rt0 = rt_first + rg * RT;                                 // its first rank tile
     if (p0 >= UV) return;  // waves never wait for each other (ES: the whole workgroup)
-    // its rank tiles; the products of tiles past the last run on zeros
-    const int na = RTL - rt0 < RT ? RTL - rt0 : RT;
+    // its rank tiles: wave-uniform, so a tile it does not have costs a scalar branch
+    const int na = wave_rank_tiles(RT, PART, RTL, rt0);
 
     // This lane's recurrence point (points past the grid compute on point 0, never stored).
     const int hl = lane & (PW - 1), he = lane / PW;
@@ -289,9 +292,10 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_receiver_values(Tabs<float> tb, i
     const int64_t sfo = ((int64_t)rt0 * NT + p0 / 16) * 256;
     const float *sfb = SF + sfo;
     const float *sfx = (TWO ? SFf : SF + N * jstride) + sfo;  // flipped slot, or plane 1
-    // to the end of the wave's last rank tile; a point tile past the row's end reads on into the
-    // next rank tile's values, or 0: its points are past the grid
-    const unsigned sfbytes = (unsigned)(na * NT - p0 / 16) * 1024u;
+    const unsigned sfbytes = value_bytes(na, NT, p0 / 16);
+    int pt[PT];
+#pragma unroll
+    for (int t = 0; t < PT; ++t) pt[t] = value_point_tile(PT, t, NT, p0 / 16);
     // A operands: slot vectors of the edge's rank tiles; B operands: slot
     // vectors of P, P' at the wave's points. Lane groups without a degree group take zeros for A
     // and any (finite) vector for B.
@@ -327,7 +331,7 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_receiver_values(Tabs<float> tb, i
         }
     };
     auto load_f = [&](__amdgpu_buffer_rsrc_t rs, int a, int t) {
-        return bload16<float4_t>(rs, lane * 16u, (unsigned)(a * NT + t) * 1024u);
+        return bload16<float4_t>(rs, lane * 16u, value_offset(a, pt[t], NT));
     };
     struct Next {
         __amdgpu_buffer_rsrc_t f, x, a, ag;
@@ -362,6 +366,7 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_receiver_values(Tabs<float> tb, i
             const float dxt = dxs[16 * t], dpt = dxs[PW + 16 * t];
 #pragma unroll
             for (int a = 0; a < RT; ++a) {
+                if (PART && a >= na) continue;
                 float4_t va = float4_t{0.f, 0.f, 0.f, 0.f}, gg = va;
                 // the small part products first
 #pragma unroll
@@ -403,6 +408,7 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_receiver_values(Tabs<float> tb, i
             const Next nx = next_edge(e0);
 #pragma unroll
             for (int a = 0; a < RT; ++a) {
+                if (PART && a >= na) continue;
                 load_a(nx.a, a, A[a]);
                 if (SPLIT) load_a(nx.ag, a, Ag[a]);
 #pragma unroll
@@ -462,7 +468,7 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_receiver_values(Tabs<float> tb, i
         if (p >= UV) continue;
 #pragma unroll
         for (int a = 0; a < RT; ++a) {
-            if (a >= na) continue;
+            if (PART && a >= na) continue;
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) {
                 float *o = S + (i * R + 16 * (rt0 + a) + 4 * g + jj) * NF * (int64_t)UVs + p;
@@ -485,7 +491,7 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_receiver_values(Tabs<float> tb, i
 // a constant no finite input sums to by chance, which keeps every load live.
 template <int RT, int PT>
 __global__ __launch_bounds__(64 * waves_for(false, RT)) void k_gather_probe_values(
-    int UV, int UVs, int R, int nchunks, int64_t N, const int32_t *__restrict__ row_ptr,
+    int UV, int UVs, int R, int rt_first, int nchunks, int64_t N, const int32_t *__restrict__ row_ptr,
     const int32_t *__restrict__ col, const int32_t *__restrict__ order,
     const float *__restrict__ SF, float *__restrict__ sink)
 {
@@ -496,9 +502,9 @@ __global__ __launch_bounds__(64 * waves_for(false, RT)) void k_gather_probe_valu
     if (!recv_chunk_block(N, order, nchunks, rg, i, ch)) return;
     const int p0 = (ch * waves_for(false, RT) + wave) * 16 * PT;
     if (p0 >= UV) return;
-    const int na = R / 16 - rg * RT < RT ? R / 16 - rg * RT : RT;
-    const float *sfb = SF + ((int64_t)rg * RT * NT + p0 / 16) * 256;
-    const unsigned bytes = (unsigned)(na * NT - p0 / 16) * 1024u;
+    const int rt0 = rt_first + rg * RT;
+    const float *sfb = SF + ((int64_t)rt0 * NT + p0 / 16) * 256;
+    const unsigned bytes = value_bytes(RT, NT, p0 / 16);
     const int64_t jstride = (int64_t)R * UVs;
     float4_t acc = float4_t{0.f, 0.f, 0.f, 0.f};
     const int e0 = row_ptr[i], e1 = row_ptr[i + 1];
@@ -509,74 +515,74 @@ __global__ __launch_bounds__(64 * waves_for(false, RT)) void k_gather_probe_valu
         for (int a = 0; a < RT; ++a)
 #pragma unroll
             for (int t = 0; t < PT; ++t)
-                if (a < na) acc += bload16<float4_t>(rs, lane * 16u, (unsigned)(a * NT + t) * 1024u);
+                acc += bload16<float4_t>(rs, lane * 16u,
+                                         value_offset(a, value_point_tile(PT, t, NT, p0 / 16), NT));
     }
     const float sum = acc[0] + acc[1] + acc[2] + acc[3];
     if (sum == -1.2345678e30f) sink[0] = sum;
 }
 
-// Rank tiles of a wave: as many as R has up to four (they share a recurrence). A wave holds
-// eight tiles (rank x point), whose sums fill half of the registers of two waves per SIMD; four,
-// two by two, with two node slots (twice the sums) or two coefficient sets (1,024-element waves of
-// four rank tiles took 4.6 -> 5.4 ms with two slots, 5,000 nodes, lmax 6, R = 128).
-int rank_tiles(int R, bool half)
-{
-    const int tiles = R / 16;
-    return tiles == 1 ? 1 : tiles == 2 || half ? 2 : 4;
-}
+// Tiles (rank x point) of all receivers, over those of a wave (eight, four of a single rank
+// tile), below which a receiver's edges are split over the waves of a workgroup: with fewer the
+// waves would not fill the 1024 SIMDs twice.
+constexpr int64_t kSplitTiles = 2048;
 
-// Tiles (rank x point) of all receivers below which a receiver's edges are split over the waves
-// of a workgroup: with fewer the waves, eight tiles each, would not fill the 1024 SIMDs twice.
-constexpr int64_t kSplitTiles = 8 * 2048;
+struct Args {
+    const Tabs<float> &tb;
+    int64_t N;
+    int R;
+    const int32_t *row_ptr, *col, *order;
+    const float *unit;
+    const void *Rt, *Rtg;
+    const float *SF, *SFf;
+    float *S;
+    hipStream_t s;
+};
 
-template <int LM, int RT, int PT, bool TWO, bool SPLIT, bool ES>
-hipError_t receiver_rt(const Tabs<float> &tb, int64_t N, int R, const int32_t *row_ptr,
-                       const int32_t *col, const int32_t *order, const float *unit,
-                       const void *Rt, const void *Rtg, const float *SF, const float *SFf,
-                       float *S, hipStream_t s)
+template <int LM, int RT, int PT, bool TWO, bool SPLIT, bool ES, bool PART = false>
+hipError_t receiver_rt(const Args &a, const RecvLaunch &l)
 {
-    const Dims &d = tb.d;
-    const int groups = (R / 16 + RT - 1) / RT, waves = ES ? kSplitWaves : waves_for(SPLIT, RT);
+    if (l.rt != RT || l.pt != PT || (l.part && !PART)) return hipErrorInvalidValue;
+    const Dims &d = a.tb.d;
+    const int waves = ES ? kSplitWaves : waves_for(SPLIT, RT);
     const int chunk = 16 * PT * (ES ? 1 : waves), nchunks = (d.UV + chunk - 1) / chunk;
-    const int64_t blocks = recv_blocks(N, (int64_t)groups * nchunks);
+    const int64_t blocks = recv_blocks(a.N, (int64_t)l.groups * nchunks);
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     size_t lds = (size_t)waves * wave_bytes(rt_groups(LM));
     const size_t sums = (size_t)kSplitWaves * RT * PT * 1024;
     if (ES && lds < sums) lds = sums;
     if (lds > (size_t)d.lds_max) return hipErrorNotSupported;
-    hipLaunchKernelGGL((k_receiver_values<LM, RT, PT, TWO, SPLIT, ES>), dim3((unsigned)blocks),
-                       dim3(64 * waves), lds, s, tb, R, nchunks, N, row_ptr, col, order, unit, Rt,
-                       Rtg, SF, SFf, S);
+    hipLaunchKernelGGL((k_receiver_values<LM, RT, PT, TWO, SPLIT, ES, PART>),
+                       dim3((unsigned)blocks), dim3(64 * waves), lds, a.s, a.tb, a.R, l.first,
+                       nchunks, a.N, a.row_ptr, a.col, a.order, a.unit, a.Rt, a.Rtg, a.SF, a.SFf,
+                       a.S);
     return hipGetLastError();
 }
 
-template <int LM>
-hipError_t receiver_lm(const Tabs<float> &tb, int64_t N, int R, const int32_t *row_ptr,
-                       const int32_t *col, const int32_t *order, const float *unit,
-                       const void *Rt, const void *Rtg, const float *SF, const float *SFf,
-                       float *S, hipStream_t s)
+template <int LM, bool TWO, bool SPLIT>
+hipError_t receiver_lm(const Args &a)
 {
-    const int rt = rank_tiles(R, SFf || Rtg);
-#define CGTP_LAUNCH(RTV, PTV, TW, SP, ESV)                                                       \
-    return receiver_rt<LM, RTV, PTV, TW, SP, ESV>(tb, N, R, row_ptr, col, order, unit, Rt, Rtg,  \
-                                                  SF, SFf, S, s)
-    if (N * (R / 16) * (tb.d.UVs / 16) < kSplitTiles) {
-        if (SFf) CGTP_LAUNCH(2, 2, true, false, true);
-        if (Rtg) CGTP_LAUNCH(2, 2, false, true, true);
-        CGTP_LAUNCH(2, 2, false, false, true);
+    const int tiles = a.R / 16;
+    constexpr bool half = TWO || SPLIT;
+    const bool es = a.N * tiles * (a.tb.d.UVs / 16) < kSplitTiles * (tiles == 1 ? 4 : 8);
+    RecvLaunch l[2];
+    const int n = recv_launches(tiles, half, es, l);
+    if (es)
+        return l[0].rt == 1 ? receiver_rt<LM, 1, 4, TWO, SPLIT, true>(a, l[0])
+                            : receiver_rt<LM, 2, 2, TWO, SPLIT, true, true>(a, l[0]);
+    for (int k = 0; k < n; ++k) {
+        hipError_t e = hipErrorInvalidValue;
+        if (l[k].rt == 1) e = receiver_rt<LM, 1, 4, TWO, SPLIT, false>(a, l[k]);
+        if constexpr (half) {
+            if (l[k].rt == 2) e = receiver_rt<LM, 2, 2, TWO, SPLIT, false>(a, l[k]);
+        } else {
+            if (l[k].rt == 2) e = receiver_rt<LM, 2, 4, false, false, false>(a, l[k]);
+            if (l[k].rt == 3) e = receiver_rt<LM, 3, 2, false, false, false>(a, l[k]);
+            if (l[k].rt == 4) e = receiver_rt<LM, 4, 2, false, false, false>(a, l[k]);
+        }
+        if (e != hipSuccess) return e;
     }
-    if (SFf) {
-        if (rt == 1) CGTP_LAUNCH(1, 4, true, false, false);
-        CGTP_LAUNCH(2, 2, true, false, false);
-    }
-    if (Rtg) {
-        if (rt == 1) CGTP_LAUNCH(1, 4, false, true, false);
-        CGTP_LAUNCH(2, 2, false, true, false);
-    }
-    if (rt == 1) CGTP_LAUNCH(1, 4, false, false, false);
-    if (rt == 2) CGTP_LAUNCH(2, 4, false, false, false);
-    CGTP_LAUNCH(4, 2, false, false, false);
-#undef CGTP_LAUNCH
+    return hipSuccess;
 }
 
 }  // namespace
@@ -589,9 +595,12 @@ hipError_t launch_receiver_values(const Tabs<float> &tb, int64_t N, int R, const
     if (N == 0) return hipSuccess;
     if (R % 16 != 0 || !sender_mfma_supported(tb.d)) return hipErrorNotSupported;
     if (SFf && Rtg) return hipErrorInvalidValue;
+    const Args a{tb, N, R, row_ptr, col, order, unit, Rt, Rtg, SF, SFf, S, s};
     switch (tb.d.lmax) {
-#define CGTP_CASE(LMV) \
-    case LMV: return receiver_lm<LMV>(tb, N, R, row_ptr, col, order, unit, Rt, Rtg, SF, SFf, S, s);
+#define CGTP_CASE(LMV)                                                                           \
+    case LMV:                                                                                    \
+        return SFf ? receiver_lm<LMV, true, false>(a)                                            \
+                   : Rtg ? receiver_lm<LMV, false, true>(a) : receiver_lm<LMV, false, false>(a);
         CGTP_CASE(0) CGTP_CASE(1) CGTP_CASE(2) CGTP_CASE(3) CGTP_CASE(4) CGTP_CASE(5) CGTP_CASE(6)
         CGTP_CASE(7) CGTP_CASE(8) CGTP_CASE(9) CGTP_CASE(10) CGTP_CASE(11) CGTP_CASE(12)
         CGTP_CASE(13) CGTP_CASE(14) CGTP_CASE(15) CGTP_CASE(16) CGTP_CASE(17) CGTP_CASE(18)
@@ -607,23 +616,22 @@ hipError_t launch_gather_probe_values(const Dims &d, int64_t N, int R, const int
 {
     if (R % 16 != 0) return hipErrorNotSupported;
     if (N == 0) return hipSuccess;
-#define CGTP_LAUNCH(RTV, PTV)                                                                    \
-    {                                                                                            \
-        constexpr int waves = waves_for(false, RTV);                                             \
-        const int groups = (R / 16 + RTV - 1) / RTV, chunk = 16 * PTV * waves;                   \
+    RecvLaunch l[2];
+    const int n = recv_launches(R / 16, false, false, l);
+#define CGTP_CASE(RTV, PTV)                                                                      \
+    case RTV: {                                                                                  \
+        constexpr int waves = waves_for(false, RTV), chunk = 16 * PTV * waves;                   \
         const int nchunks = (d.UV + chunk - 1) / chunk;                                          \
-        const int64_t blocks = recv_blocks(N, (int64_t)groups * nchunks);                        \
+        const int64_t blocks = recv_blocks(N, (int64_t)l[k].groups * nchunks);                   \
         if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;                                  \
         hipLaunchKernelGGL((k_gather_probe_values<RTV, PTV>), dim3((unsigned)blocks),            \
-                           dim3(64 * waves), 0, s, d.UV, d.UVs, R, nchunks, N, row_ptr, col,    \
-                           order, SF, sink);                                                     \
+                           dim3(64 * waves), 0, s, d.UV, d.UVs, R, l[k].first, nchunks, N,      \
+                           row_ptr, col, order, SF, sink);                                       \
+        break;                                                                                   \
     }
-    switch (rank_tiles(R, false)) {
-    case 4: CGTP_LAUNCH(4, 2) break;
-    case 2: CGTP_LAUNCH(2, 4) break;
-    default: CGTP_LAUNCH(1, 4) break;
-    }
-#undef CGTP_LAUNCH
+    for (int k = 0; k < n; ++k)
+        switch (l[k].rt) { CGTP_CASE(1, 4) CGTP_CASE(2, 4) CGTP_CASE(3, 2) CGTP_CASE(4, 2) }
+#undef CGTP_CASE
     return hipGetLastError();
 }
 

@@ -27,7 +27,8 @@ def cg():
 
 
 def _tiles(n, lmax, R):
-    """Rank tiles x point tiles of all receivers: below 16384 the edges are split over waves."""
+    """Rank tiles x point tiles of all receivers: below 16384 (8192 with a single rank tile) the
+    edges are split over waves."""
     uv = ((3 * lmax + 3) // 2) * (3 * lmax + 1)
     return n * ((R + 15) // 16) * ((uv + 31) // 32 * 2)
 
@@ -40,8 +41,12 @@ SHAPES = [(0, 16, 60), (3, 9, 60), (7, 40, 40), (15, 16, 20), (24, 24, 20),
 @pytest.mark.parametrize("slots", ["one", "two", "blocks"])
 @pytest.mark.parametrize("lmax,R,n", SHAPES)
 def test_receiver_values_tiles(cg, lmax, R, n, slots):
-    split = _tiles(n, lmax, R) < 16384
+    split = _tiles(n, lmax, R) < (8192 if R <= 16 else 16384)
     assert split == (SHAPES.index((lmax, R, n)) < 5)
+    check_receiver(cg, lmax, R, n, slots)
+
+
+def check_receiver(cg, lmax, R, n, slots):
     C, r_cut = 5, 2.6
     rows = sample_rows(n, 10 if lmax < 15 else 3, seed=lmax)
     if slots == "blocks":
@@ -62,6 +67,20 @@ def test_receiver_values_tiles(cg, lmax, R, n, slots):
                               node_flip=d.get("node_flip"))
     for a, b in zip(got, ref):
         assert rel_err(a[rows], b) <= TOL_F32
+
+
+# Rank tiles that no group of two or four divides, one per way they are cut (3; 3 + 2; 4 + 3; with
+# half a wave's tiles 2 + 1), a single one, and rows whose point tiles four do not divide (lmax 5
+# and 7), each at a degree of one, two and three degree groups; nodes for the form that splits the
+# edges and for the one that does not.
+CUTS = [(5, 32, 30), (5, 32, 900), (7, 16, 500), (17, 80, 20), (17, 80, 60), (6, 112, 400),
+        (9, 48, 200), (10, 144, 80), (20, 16, 150)]
+
+
+@pytest.mark.parametrize("slots", ["one", "two", "blocks"])
+@pytest.mark.parametrize("lmax,R,n", CUTS)
+def test_receiver_values_cut_ranks(cg, lmax, R, n, slots):
+    check_receiver(cg, lmax, R, n, slots)
 
 
 def test_receiver_without_edges_among_others(cg):
