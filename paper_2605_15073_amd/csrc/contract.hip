@@ -223,9 +223,8 @@ constexpr int kSW = kTile + 16;  // LDS row stride of Ws: lane groups of a half-
 constexpr int kNX = kTile * kCk * kLG / kThreadsC;  // staged elements per thread and slice
 
 // PARTS: the output as bf16 triples in the slot vectors of the values-only receiver,
-// Yp [B][rtiles][3][ndg][16 ranks][8 degrees] (4 up to lmax 3), ranks r0 + o (zeros for o in
-// [Cout, oend)): a lane's kLG = 4 degrees of one rank are half a slot vector (or a whole one of
-// 4), one 8-byte store per part.
+// Yp [B][rtiles][3][ndg][16 ranks][8 degrees], ranks r0 + o (zeros for o in [Cout, oend)): a
+// lane's kLG = 4 degrees of one rank are half a slot vector, one 8-byte store per part.
 template <bool PARTS>
 __global__ __launch_bounds__(kThreadsC, 4) void k_contract_kdeg(
     int64_t B, int Cin, int Cout, int L, int otiles, int lgroups, const float *__restrict__ W,
@@ -323,7 +322,8 @@ __global__ __launch_bounds__(kThreadsC, 4) void k_contract_kdeg(
         float sc[kLG];
 #pragma unroll
         for (int l = 0; l < kLG; ++l) sc[l] = l < nl ? scale[l0 + l] : 0.f;
-        const int ndg = rt_groups(L - 1), vw = rt_vec_bytes(L - 1) / 8;
+        constexpr int vw = 2;  // 8-byte words of a slot vector
+        const int ndg = rt_groups(L - 1);
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
             const int o = o0 + wo + 16 * c + n, r = r0 + o;
@@ -470,7 +470,7 @@ hipError_t launch_contract_edge_parts(int64_t B, int Cin, int Cout, int L, const
     const int64_t groups = (B + kTile - 1) / kTile;
     const int oend = rend - r0;
     const int otiles = (oend + kTile - 1) / kTile;
-    const int lgroups = rt_groups(L - 1) * rt_vec_bytes(L - 1) / (2 * kLG);
+    const int lgroups = rt_groups(L - 1) * kRtPart / kLG;
     const int64_t blocks = groups * otiles * lgroups;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const int64_t x_sb = (int64_t)Cin * L;

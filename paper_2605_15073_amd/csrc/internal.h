@@ -106,16 +106,33 @@ hipError_t launch_contract<double>(int64_t, int, int, int, bool, const double *,
                                    int64_t, const double *, int64_t, double *, int64_t, int64_t,
                                    int64_t, const double *, bool, hipStream_t);
 
-// Edge coefficients of the values-only receiver (receiver_values.hip): the kdeg contraction
-// above (with scale) into ranks [r0, r0 + Cout) of Y [B][R/16][3][rt_groups][16 ranks][8] bf16,
-// each value as the exact sum of three bf16 parts, a slot vector holding 8 degrees of one part
-// (4 up to lmax 3; zero past lmax). Ranks [r0 + Cout, rend) are written as zeros.
+// Edge coefficients of the values-only receiver (receiver_values.hip), R a multiple of 16. As
+// floats [E][L][R] (receiver_values_f32), from launch_contract's kdeg form; otherwise each value
+// as the sum of three bf16 parts, Y [B][R/16][3][rt_groups][16 ranks][8] bf16, a slot vector
+// holding 8 degrees of one part (zero past lmax), from launch_contract_edge_parts: the kdeg
+// contraction (with scale) into ranks [r0, r0 + Cout), and zeros into [r0 + Cout, rend).
 constexpr int kRtPart = 8;
 __host__ __device__ constexpr int rt_groups(int lmax) { return lmax / kRtPart + 1; }
-__host__ __device__ constexpr int rt_vec_bytes(int lmax) { return lmax < 4 ? 8 : 16; }
-inline size_t rt_parts_bytes(int lmax, int64_t E, int R)
+// The receiver's fp32 form, where the bf16 one's slot vectors of eight degrees and its split of P
+// into parts cost more than its faster products save (edge contraction + receiver, bf16 and fp32
+// form; 128 channels and ranks but where stated, 52 edges a node):
+//   up to lmax 4, one or two fp32 steps a product: 8,000 nodes, lmax 2 1588 and 1372 us, lmax 3
+//   2136 and 1900; 6,000 nodes, lmax 4 2883 and 2756;
+//   at lmax 8, nine degrees in sixteen slots: 2,500 nodes 4123 and 3747;
+//   a single rank tile, which pays the split alone: 32 channels, 27 edges a node, lmax 10,
+//   500 nodes 121 and 89 us, lmax 18, 250 nodes 250 and 190 (receiver);
+//   with per-block factors (split), which hold two sets of coefficients, but where the degrees
+//   fill the slots of two groups: 64 channels, 32 ranks of 4 blocks, 1,300 nodes, lmax 6 932 and
+//   823 us; 500 nodes, lmax 11 1230 and 1139; 300 nodes, lmax 13 991 and 1026; 250 nodes, lmax 15
+//   1082 and 1113; 333 nodes, lmax 16 1826 and 1669.
+constexpr bool receiver_values_f32(int lmax, int R, bool split)
 {
-    return (size_t)E * R * 3 * rt_groups(lmax) * rt_vec_bytes(lmax);
+    return lmax <= 4 || lmax == 8 || R == 16 || (split && (lmax < 12 || lmax > 15));
+}
+inline size_t rt_bytes(int lmax, int64_t E, int R, bool split)
+{
+    return (size_t)E * R *
+           (receiver_values_f32(lmax, R, split) ? 4 * (lmax + 1) : 3 * rt_groups(lmax) * 16);
 }
 hipError_t launch_contract_edge_parts(int64_t B, int Cin, int Cout, int L, const float *W,
                                       int64_t w_sl, int64_t w_si, int64_t w_so, const float *X,

@@ -96,6 +96,13 @@ int mp_rank(const cgtp_plan_s *p, int R, bool split)
     return mfma_values_only(p, R, split) ? (R + 15) / 16 * 16 : R;
 }
 
+// Whether the edge coefficients of that form are bf16 parts (else floats).
+bool mp_edge_parts(const cgtp_plan_s *p, int R, bool split)
+{
+    return mfma_values_only(p, R, split) &&
+           !cgtp::receiver_values_f32(p->d.lmax, mp_rank(p, R, split), split);
+}
+
 // Receiver on MFMA: the values-only form above, else (three sender planes) fp32, zonal edge
 // field, R a multiple of 16, lmax high enough that the per-thread recurrence sums would make
 // the SIMT receiver compute-bound.
@@ -164,7 +171,7 @@ Layout mp_layout(const cgtp_plan_s *p, int R, int64_t N, int64_t E, bool two = f
     // values only: one plane of tiles (two with split factors); otherwise three fields
     const size_t sf_planes = mfma_values_only(p, R, split) ? (split ? 2 : 1) : 3;
     size_t sf = align256(es * (size_t)N * R * sf_planes * p->d.UVs);
-    size_t rt = align256(mfma_values_only(p, R, split) ? cgtp::rt_parts_bytes(p->d.lmax, E, R)
+    size_t rt = align256(mfma_values_only(p, R, split) ? cgtp::rt_bytes(p->d.lmax, E, R, split)
                                                        : es * (size_t)E * R * p->d.L);
     const int sg_planes = values_only_form(p, R, split) ? (two ? 6 : 3) : 2;
     size_t sg = use_mfma_receiver(p, R, split)
@@ -482,16 +489,16 @@ int run_mp(cgtp_plan_s *p, int op, int64_t N, int64_t E, const int32_t *row_ptr,
         if (e != hipSuccess) return hip_fail(e, "sender fields");
     }
     rec.mark();
-    // Eq. msgpass-tildeR into Rt [E][L][R] (the zonal form folds in the addition-theorem
-    // weight (2l+1)/(4 pi))
-    if (mfma_values_only(p, R, false))
+    // Eq. msgpass-tildeR into Rt [E][L][Rp], or in parts (the zonal form folds in the
+    // addition-theorem weight (2l+1)/(4 pi))
+    if (mp_edge_parts(p, R, false))
         e = cgtp::launch_contract_edge_parts(E, C, R, d.L, (const float *)UE, (int64_t)C * R, R, 1,
                                              (const float *)rad, Rt, Rp, 0, Rp,
                                              (const float *)tb.cl, s);
     else
         e = cgtp::launch_contract<T>(E, C, R, d.L, true, (const T *)UE, (int64_t)C * R, R, 1,
-                                     (const T *)rad, (int64_t)C * d.L, Rt, (int64_t)d.L * R, 1, R,
-                                     separated ? nullptr : tb.cl, false, s);
+                                     (const T *)rad, (int64_t)C * d.L, Rt, (int64_t)d.L * Rp, 1,
+                                     Rp, separated ? nullptr : tb.cl, false, s);
     if (e != hipSuccess) return hip_fail(e, "contract edge radial");
     rec.mark();
     {
@@ -825,7 +832,7 @@ int run_mp_groups(cgtp_plan_s *p, const Groups &G, int64_t N, int64_t E, const i
         const Group &g = G.g[gi];
         for (int pass = 0; pass < (G.split ? 2 : 1); ++pass) {
             const int blk = G.split ? (pass ? g.bc : g.bg) : group_block(g);
-            if (mfma_values_only(p, Rs, G.split))
+            if (mp_edge_parts(p, Rs, G.split))
                 e = cgtp::launch_contract_edge_parts(E, C, R, d.L, (const float *)f.in1[blk],
                                                      (int64_t)C * R, R, 1, (const float *)rad,
                                                      pass ? Rtc : Rt, Rg, gi * R,

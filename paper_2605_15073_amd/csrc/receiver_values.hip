@@ -25,6 +25,12 @@
 // pairs of it, two instructions; with two groups (lmax <= 15) two part pairs of both, three
 // instructions; above, one part pair of up to four groups, six instructions.
 //
+// fp32 form (F32). The split costs vector instructions per degree and point, paid once per wave,
+// and a slot vector costs 48 bytes per rank however few of its degrees exist. Where a wave has one
+// rank tile to share the split, or the degrees fill the slots badly, the products run on the fp32
+// instructions (16x16x4, four degrees a step) from P rows and coefficients held as floats; the
+// tiles, waves and sums are the same. receiver_values_f32 (internal.h) has the rule and both sides.
+//
 // Sender values come in tiles of 16 ranks x 16 points, 1 KB each in the order a wave reads
 // them: SF [N][R/16][UVs/16][64 lanes][4], lane 16 g + n holding ranks 4 g .. 4 g + 3 of point
 // n (with per-block factors a second such plane follows). One 16-byte load per lane then
@@ -45,9 +51,9 @@
 // R = 64, 35.0 -> 27.9 ms; two slots, 5,000 nodes, lmax 6, R = 128, 6.81 -> 4.56 ms; per-block
 // factors, 3,000 nodes, lmax 6, 128 stacked ranks, 3.78 -> 3.06 ms. What bounds it now is the
 // power limit: it needs a third fewer cycles than the fp32 form, but the clock falls from 2.05
-// to 1.75 GHz with matrix cores (31% busy), vector ALU (56%) and gather all running. A single
-// rank tile above lmax 15 pays its recurrences alone and is slower than it was (2.6 -> 3.2 ms,
-// 2,000 nodes, lmax 18, R = 16).
+// to 1.75 GHz with matrix cores (31% busy), vector ALU (56%) and gather all running.
+#include <type_traits>
+
 #include "internal.h"
 #include "receiver_tiles.h"
 
@@ -77,10 +83,19 @@ __device__ __forceinline__ V bload16(__amdgpu_buffer_rsrc_t rs, unsigned voff, u
 // A byte offset past every resource here: loads return 0.
 constexpr unsigned kOut = 0x80000000u;
 // Waves per workgroup (neighbouring points): two, so that few of them lie past the grid; four
-// with two coefficient sets, which share twice the coefficients through L1, one with a single
-// rank tile, whose 64 points are a larger share of the grid (3.05 against 3.14 ms,
-// 3,000 nodes, lmax 6, 128 stacked ranks).
-constexpr int waves_for(bool split, int rt) { return split ? 4 : rt == 1 ? 1 : 2; }
+// with two coefficient sets, which share twice the coefficients through L1 (3.05 against 3.14 ms,
+// 3,000 nodes, lmax 6, 128 stacked ranks; at lmax 24 four would take 100 KB of LDS, one workgroup
+// per compute unit), one with a single rank tile, whose 64 points are a larger share of the grid.
+constexpr int waves_for(bool split, int rt, int ndg)
+{
+    return split && ndg < 4 ? 4 : rt == 1 && !split ? 1 : 2;
+}
+// Waves per SIMD that the registers are to leave room for: two; with a single rank tile, whose
+// waves have the least to hide their latency behind, as many as its sums allow.
+constexpr int simd_waves(int lm, int rt, bool half)
+{
+    return rt > 1 || half || lm >= 24 ? 2 : lm <= 11 ? 4 : 3;
+}
 constexpr int kSplitWaves = 4;  // waves per workgroup that share one wave's edges (ES)
 
 // Wave-private LDS in bytes: 64 (edge, point) pairs, each with the slot vectors of P_l, then of
@@ -88,6 +103,15 @@ constexpr int kSplitWaves = 4;  // waves per workgroup that share one wave's edg
 // Layout [edge][P, P'][part][degree group][points][8 bf16], then [edge][2][points].
 constexpr int plane_vecs(int ndg) { return 3 * ndg + (ndg == 1 ? 1 : 0); }
 constexpr int wave_bytes(int ndg) { return 64 * (2 * plane_vecs(ndg) * 16 + 2 * 4); }
+
+// fp32 form: reduction steps of 4 degrees of the value sum and of the derivative sum. P_0' = 0:
+// where lmax is a multiple of 4 the derivative sum starts at degree f32_first = 1 and takes a
+// step fewer. Wave-private LDS: rows of P_l, then of P_l', of the 64 (edge, point) pairs, and
+// dt/dx and dt/dphi: [edge][row][points], then [edge][2][points].
+constexpr int f32_first(int lm) { return lm > 0 && lm % 4 == 0 ? 1 : 0; }
+constexpr int f32_steps(int lm) { return lm / 4 + 1; }
+constexpr int f32_dsteps(int lm) { return (lm - f32_first(lm)) / 4 + 1; }
+constexpr int f32_wave_bytes(int lm) { return 64 * 4 * (4 * (f32_steps(lm) + f32_dsteps(lm)) + 2); }
 
 // Operand vectors by degree groups. Lane group g of instruction i multiplies a part (0 h, 1 m,
 // 2 l, 3 zero) of A vector av(i) with one of B vector bv(i), of the degree group group(g):
@@ -171,15 +195,15 @@ __device__ __forceinline__ void wave_sync()
 // Table 1 its curl then feeds S_alpha's slot (natural parity) and its Gaunt product S_beta's.
 // SPLIT: per-block factors. The derivative sum g multiplies P' with the curl factors' edge
 // coefficients Rtg and its products take the curl factors' values, plane 1 of SF.
-// Rt, Rtg: edge coefficients in parts, [E][R/16][3 parts][NDG][16 ranks][8 degrees] bf16 (4
-// degrees up to lmax 3).
+// Rt, Rtg: edge coefficients in parts, [E][R/16][3 parts][NDG][16 ranks][8 degrees] bf16.
 // ES: the workgroup's waves (kSplitWaves) take one wave's tiles together, a share of the edges
 // each, and add up their sums in wave order.
 // rt_first: the first rank tile of the launch. PART: the last wave may have fewer than RT rank
 // tiles and skips the others; without it every wave has RT.
-template <int LM, int RT, int PT, bool TWO, bool SPLIT, bool ES, bool PART>
-__global__ __launch_bounds__(64 * (ES ? kSplitWaves : waves_for(SPLIT, RT)))
-__attribute__((amdgpu_waves_per_eu(2))) void k_receiver_values(Tabs<float> tb, int R, int rt_first, int nchunks, int64_t N,
+// F32: products on the fp32 matrix instructions; Rt, Rtg are [E][LM + 1][R] floats.
+template <int LM, int RT, int PT, bool TWO, bool SPLIT, bool ES, bool PART, bool F32>
+__global__ __launch_bounds__(64 * (ES ? kSplitWaves : waves_for(SPLIT, RT, rt_groups(LM))))
+__attribute__((amdgpu_waves_per_eu(simd_waves(LM, RT, TWO || SPLIT)))) void k_receiver_values(Tabs<float> tb, int R, int rt_first, int nchunks, int64_t N,
                        const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
                        const int32_t *__restrict__ order, const float *__restrict__ unit,
                        const void *__restrict__ Rt, const void *__restrict__ Rtg,
@@ -187,23 +211,30 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_receiver_values(Tabs<float> tb, i
                        float *__restrict__ S)
 {
     constexpr int NDG = rt_groups(LM);
-    // bytes of a stored slot vector, and of a rank tile's
-    constexpr int VB = rt_vec_bytes(LM), TB = 3 * NDG * 16 * VB;
+    constexpr int TB = 3 * NDG * 16 * 16;  // bytes of a rank tile's slot vectors
     using SL = Slots<NDG>;
+    constexpr int KS = f32_steps(LM), KSG = f32_dsteps(LM), DO = f32_first(LM);
+    constexpr bool AG = SPLIT || (F32 && DO);  // the derivative sum has operands of its own
+    constexpr int NA = F32 ? KS : SL::NA, NB = F32 ? KS : SL::NB;
+    using vec_t = typename std::conditional<F32, float, bf8_t>::type;  // one lane's operand
     constexpr int PW = 16 * PT, EG = 64 / PW;  // points of a wave, edges per recurrence pass
-    constexpr int PLANE = plane_vecs(NDG) * PW * 16;  // P's or P''s vectors of one edge
-    constexpr int DXS = EG * 2 * PLANE;               // byte offset of dt/dx, dt/dphi
+    // bytes of one edge's P vectors (rows) and of both, and where dt/dx and dt/dphi start
+    constexpr int PLANE = F32 ? 4 * KS * PW * 4 : plane_vecs(NDG) * PW * 16;
+    constexpr int PLANES = F32 ? PLANE + 4 * KSG * PW * 4 : 2 * PLANE, DXS = EG * PLANES;
     const Dims &d = tb.d;
     const int UV = d.UV, UVs = d.UVs, NT = UVs / 16, RTL = R / 16;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4, n = lane & 15;
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    char *lds = smem + wave * wave_bytes(NDG);
+    char *lds = smem + wave * (F32 ? f32_wave_bytes(LM) : wave_bytes(NDG));
+    // fp32 rows: column of point p in row j. The two rows that half a wave reads at once lie on
+    // different halves of the banks, and a row's writes stay a permutation of them.
+    auto fslot = [](int j, int p) { return j * PW + (p ^ ((j & (PT - 1)) << 4)); };
 
     int64_t i;
     int rg, ch;
     if (!recv_chunk_block(N, order, nchunks, rg, i, ch)) return;  // the whole workgroup
-    const int p0 = (ES ? ch : ch * waves_for(SPLIT, RT) + wave) * PW;  // first point of the wave
+    const int p0 = (ES ? ch : ch * waves_for(SPLIT, RT, NDG) + wave) * PW;  // first point of the wave
     const int rt0 = rt_first + rg * RT;                                 // its first rank tile
     if (p0 >= UV) return;  // waves never wait for each other (ES: the whole workgroup)
     // its rank tiles: wave-uniform, so a tile it does not have costs a scalar branch
@@ -242,7 +273,8 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_receiver_values(Tabs<float> tb, i
         float *dxs = reinterpret_cast<float *>(lds + DXS) + he * 2 * PW + hl;
         dxs[0] = uz - rxsx * h;
         dxs[PW] = rsx * (uy * rcp - ux * rsp);
-        uint4_t *o = reinterpret_cast<uint4_t *>(lds + he * 2 * PLANE) + hl;
+        uint4_t *o = reinterpret_cast<uint4_t *>(lds + he * PLANES) + hl;
+        float *of = reinterpret_cast<float *>(lds + he * PLANES);
         // P_l = ((2l-1) t P_{l-1} - (l-1) P_{l-2}) / l,  P_l' = l P_{l-1} + t P_{l-1}' (the form
         // P_{l-2}' + (2l-1) P_{l-1} is one operation shorter and measured less accurate)
         float p0v = 0.f, p1v = 0.f, d1 = 0.f;  // P_{l-2}, P_{l-1}, P_{l-1}'
@@ -263,10 +295,15 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_receiver_values(Tabs<float> tb, i
                 }
                 v[k] = p2;
                 w[k] = d2;
+                if (F32) {
+                    of[fslot(l, hl)] = p2;
+                    if (l >= DO) of[4 * KS * PW + fslot(l - DO, hl)] = d2;
+                }
                 p0v = p1v;
                 p1v = p2;
                 d1 = d2;
             }
+            if (F32) continue;
             uint4_t part[3];
             split8(v, part);
 #pragma unroll
@@ -299,16 +336,28 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_receiver_values(Tabs<float> tb, i
     // A operands: slot vectors of the edge's rank tiles; B operands: slot
     // vectors of P, P' at the wave's points. Lane groups without a degree group take zeros for A
     // and any (finite) vector for B.
-    unsigned ao[SL::NA], bo[SL::NB];
+    // F32: A degree 4 k + g (zero past lmax) of rank n, B the same row at point n.
+    unsigned ao[NA], ago[NA], bo[NB];
     const int dgl = SL::group(g);
 #pragma unroll
-    for (int k = 0; k < SL::NA; ++k)
-        ao[k] = dgl < NDG ? (unsigned)((SL::apart(k, g) * NDG + dgl) * 16 + n) * VB : kOut;
+    for (int k = 0; k < NA; ++k) {
+        if constexpr (F32) {
+            ao[k] = 4 * k + g <= LM ? (unsigned)((4 * k + g) * R + n) * 4u : kOut;
+            ago[k] = 4 * k + g + DO <= LM ? (unsigned)((4 * k + g + DO) * R + n) * 4u : kOut;
+        } else {
+            ao[k] = ago[k] = dgl < NDG ? (unsigned)((SL::apart(k, g) * NDG + dgl) * 16 + n) * 16u : kOut;
+        }
+    }
 #pragma unroll
-    for (int k = 0; k < SL::NB; ++k)
-        bo[k] = (unsigned)((SL::bpart(k, g) * NDG + (dgl < NDG ? dgl : 0)) * (PW * 16) + n * 16);
-    const char *rtb = static_cast<const char *>(Rt) + rt0 * TB;
-    const char *rtgb = static_cast<const char *>(Rtg) + (SPLIT ? rt0 * TB : 0);
+    for (int k = 0; k < NB; ++k)
+        bo[k] = F32 ? 0u : (unsigned)((SL::bpart(k, g) * NDG + (dgl < NDG ? dgl : 0)) * (PW * 16) + n * 16);
+    // an edge's coefficients from the wave's first rank tile on, a rank tile's bytes, an edge's
+    // and those up to the wave's last rank tile
+    constexpr unsigned TA = F32 ? 16 * 4 : TB;
+    const char *rtb = static_cast<const char *>(Rt) + rt0 * TA;
+    const char *rtgb = static_cast<const char *>(Rtg) + (SPLIT ? rt0 * TA : 0);
+    const int64_t estride = F32 ? (int64_t)(LM + 1) * R * 4 : (int64_t)RTL * TB;
+    const unsigned abytes = F32 ? (unsigned)(LM * R) * 4u + na * TA : na * TA;
 
     // sender indices in batches of 64 edges: lane k holds that of edge k of the batch, read out
     // with readlane, so no load of an index sits on an edge's critical path (coln: the next 64)
@@ -317,17 +366,17 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_receiver_values(Tabs<float> tb, i
     // An edge's values and coefficients are requested one edge ahead, tile by tile, each right
     // after its registers' last use (past the last edge the last is requested again).
     float4_t f[RT][PT], x[RT][PT];
-    bf8_t A[RT][SL::NA], Ag[RT][SL::NA];
-    auto load_a = [&](__amdgpu_buffer_rsrc_t rs, int a, bf8_t (&v)[SL::NA]) {
+    vec_t A[RT][NA], Ag[AG ? RT : 1][NA];
+    auto load_a = [&](__amdgpu_buffer_rsrc_t rs, int a, const unsigned (&off)[NA], int steps,
+                      vec_t (&v)[NA]) {
 #pragma unroll
-        for (int k = 0; k < SL::NA; ++k) {
-            if constexpr (VB == 16) {
-                v[k] = bload16<bf8_t>(rs, ao[k], (unsigned)(a * TB));
-            } else {  // half vectors: four degrees
-                const uint2_t w = __builtin_bit_cast(
-                    uint2_t, __builtin_amdgcn_raw_buffer_load_b64(rs, ao[k], (unsigned)(a * TB), 0));
-                v[k] = __builtin_bit_cast(bf8_t, uint4_t{w[0], w[1], 0, 0});
-            }
+        for (int k = 0; k < NA; ++k) {
+            if (k >= steps) continue;
+            if constexpr (F32)
+                v[k] = __builtin_bit_cast(
+                    float, __builtin_amdgcn_raw_buffer_load_b32(rs, off[k], (unsigned)a * TA, 0));
+            else
+                v[k] = bload16<bf8_t>(rs, off[k], (unsigned)a * TA);
         }
     };
     auto load_f = [&](__amdgpu_buffer_rsrc_t rs, int a, int t) {
@@ -347,38 +396,55 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_receiver_values(Tabs<float> tb, i
         Next r;
         r.f = rsrc(sfb + j * jstride, sfbytes);
         r.x = rsrc(sfx + j * jstride, sfbytes);
-        r.a = rsrc(rtb + (int64_t)ec * RTL * TB, (unsigned)(na * TB));
-        r.ag = rsrc(rtgb + (int64_t)ec * RTL * TB, (unsigned)(na * TB));
+        r.a = rsrc(rtb + ec * estride, abytes);
+        r.ag = SPLIT ? rsrc(rtgb + ec * estride, abytes) : r.a;
         return r;
     };
     auto edge = [&](int e, int q) {
         const Next nx = next_edge(e + 1);
-        const char *u = lds + q * 2 * PLANE;
+        const char *u = lds + q * PLANES;
         const float *dxs = reinterpret_cast<const float *>(lds + DXS) + q * 2 * PW + n;
 #pragma unroll
         for (int t = 0; t < PT; ++t) {
-            bf8_t pv[SL::NB], dv[SL::NB];
+            vec_t pv[NB], dv[NB];
 #pragma unroll
-            for (int k = 0; k < SL::NB; ++k) {
-                pv[k] = *reinterpret_cast<const bf8_t *>(u + bo[k] + t * 256);
-                dv[k] = *reinterpret_cast<const bf8_t *>(u + PLANE + bo[k] + t * 256);
+            for (int k = 0; k < NB; ++k) {
+                if constexpr (F32) {
+                    const int at = fslot(4 * k + g, 16 * t + n);
+                    pv[k] = reinterpret_cast<const float *>(u)[at];
+                    if (k < KSG) dv[k] = reinterpret_cast<const float *>(u + PLANE)[at];
+                } else {
+                    pv[k] = *reinterpret_cast<const bf8_t *>(u + bo[k] + t * 256);
+                    dv[k] = *reinterpret_cast<const bf8_t *>(u + PLANE + bo[k] + t * 256);
+                }
             }
             const float dxt = dxs[16 * t], dpt = dxs[PW + 16 * t];
 #pragma unroll
             for (int a = 0; a < RT; ++a) {
                 if (PART && a >= na) continue;
                 float4_t va = float4_t{0.f, 0.f, 0.f, 0.f}, gg = va;
-                // the small part products first
+                if constexpr (F32) {
 #pragma unroll
-                for (int k = SL::NI - 1; k >= 0; --k) {
-                    va = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[a][SL::av(k)], pv[SL::bv(k)],
-                                                                 va, 0, 0, 0);
-                    gg = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                        SPLIT ? Ag[a][SL::av(k)] : A[a][SL::av(k)], dv[SL::bv(k)], gg, 0, 0, 0);
+                    for (int k = 0; k < KS; ++k) {
+                        va = __builtin_amdgcn_mfma_f32_16x16x4f32(A[a][k], pv[k], va, 0, 0, 0);
+                        if (k < KSG)
+                            gg = __builtin_amdgcn_mfma_f32_16x16x4f32(AG ? Ag[AG ? a : 0][k] : A[a][k],
+                                                                      dv[k], gg, 0, 0, 0);
+                    }
+                } else {
+                    // the small part products first
+#pragma unroll
+                    for (int k = SL::NI - 1; k >= 0; --k) {
+                        va = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[a][SL::av(k)], pv[SL::bv(k)],
+                                                                     va, 0, 0, 0);
+                        gg = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            AG ? Ag[AG ? a : 0][SL::av(k)] : A[a][SL::av(k)], dv[SL::bv(k)], gg, 0,
+                            0, 0);
+                    }
                 }
                 if (t == PT - 1) {
-                    load_a(nx.a, a, A[a]);
-                    if (SPLIT) load_a(nx.ag, a, Ag[a]);
+                    load_a(nx.a, a, ao, NA, A[a]);
+                    if (AG) load_a(nx.ag, a, ago, F32 ? KSG : NA, Ag[AG ? a : 0]);
                 }
 #pragma unroll
                 for (int jj = 0; jj < 4; ++jj) {
@@ -409,8 +475,8 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_receiver_values(Tabs<float> tb, i
 #pragma unroll
             for (int a = 0; a < RT; ++a) {
                 if (PART && a >= na) continue;
-                load_a(nx.a, a, A[a]);
-                if (SPLIT) load_a(nx.ag, a, Ag[a]);
+                load_a(nx.a, a, ao, NA, A[a]);
+                if (AG) load_a(nx.ag, a, ago, F32 ? KSG : NA, Ag[AG ? a : 0]);
 #pragma unroll
                 for (int t = 0; t < PT; ++t) {
                     f[a][t] = load_f(nx.f, a, t);
@@ -418,10 +484,17 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_receiver_values(Tabs<float> tb, i
                 }
             }
         }
-        if (NDG == 1) {  // the zero vectors
+        if (F32) {  // the rows past lmax, which the A operands take zero times
+#pragma unroll
+            for (int j = LM + 1; j < 4 * KS; ++j)
+                reinterpret_cast<float *>(lds + he * PLANES)[fslot(j, hl)] = 0.f;
+#pragma unroll
+            for (int j = LM + 1 - DO; j < 4 * KSG; ++j)
+                reinterpret_cast<float *>(lds + he * PLANES + PLANE)[fslot(j, hl)] = 0.f;
+        } else if (NDG == 1) {  // the zero vectors
 #pragma unroll
             for (int k = 0; k < 2; ++k)
-                *reinterpret_cast<uint4_t *>(lds + (he * 2 + k) * PLANE + (3 * PW + hl) * 16) =
+                *reinterpret_cast<uint4_t *>(lds + he * PLANES + k * PLANE + (3 * PW + hl) * 16) =
                     uint4_t{0, 0, 0, 0};
         }
         for (int b = e0; b < e1; b += EG) {
@@ -490,7 +563,7 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_receiver_values(Tabs<float> tb, i
 // nothing computed from them but a running sum; sink receives a value only if that sum equals
 // a constant no finite input sums to by chance, which keeps every load live.
 template <int RT, int PT>
-__global__ __launch_bounds__(64 * waves_for(false, RT)) void k_gather_probe_values(
+__global__ __launch_bounds__(64 * waves_for(false, RT, 1)) void k_gather_probe_values(
     int UV, int UVs, int R, int rt_first, int nchunks, int64_t N, const int32_t *__restrict__ row_ptr,
     const int32_t *__restrict__ col, const int32_t *__restrict__ order,
     const float *__restrict__ SF, float *__restrict__ sink)
@@ -500,7 +573,7 @@ __global__ __launch_bounds__(64 * waves_for(false, RT)) void k_gather_probe_valu
     int64_t i;
     int rg, ch;
     if (!recv_chunk_block(N, order, nchunks, rg, i, ch)) return;
-    const int p0 = (ch * waves_for(false, RT) + wave) * 16 * PT;
+    const int p0 = (ch * waves_for(false, RT, 1) + wave) * 16 * PT;
     if (p0 >= UV) return;
     const int rt0 = rt_first + rg * RT;
     const float *sfb = SF + ((int64_t)rt0 * NT + p0 / 16) * 256;
@@ -539,20 +612,20 @@ struct Args {
     hipStream_t s;
 };
 
-template <int LM, int RT, int PT, bool TWO, bool SPLIT, bool ES, bool PART = false>
+template <int LM, int RT, int PT, bool TWO, bool SPLIT, bool F32, bool ES, bool PART = false>
 hipError_t receiver_rt(const Args &a, const RecvLaunch &l)
 {
     if (l.rt != RT || l.pt != PT || (l.part && !PART)) return hipErrorInvalidValue;
     const Dims &d = a.tb.d;
-    const int waves = ES ? kSplitWaves : waves_for(SPLIT, RT);
+    constexpr int ndg = rt_groups(LM), waves = ES ? kSplitWaves : waves_for(SPLIT, RT, ndg);
     const int chunk = 16 * PT * (ES ? 1 : waves), nchunks = (d.UV + chunk - 1) / chunk;
     const int64_t blocks = recv_blocks(a.N, (int64_t)l.groups * nchunks);
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    size_t lds = (size_t)waves * wave_bytes(rt_groups(LM));
+    size_t lds = (size_t)waves * (F32 ? f32_wave_bytes(LM) : wave_bytes(ndg));
     const size_t sums = (size_t)kSplitWaves * RT * PT * 1024;
     if (ES && lds < sums) lds = sums;
     if (lds > (size_t)d.lds_max) return hipErrorNotSupported;
-    hipLaunchKernelGGL((k_receiver_values<LM, RT, PT, TWO, SPLIT, ES, PART>),
+    hipLaunchKernelGGL((k_receiver_values<LM, RT, PT, TWO, SPLIT, ES, PART, F32>),
                        dim3((unsigned)blocks), dim3(64 * waves), lds, a.s, a.tb, a.R, l.first,
                        nchunks, a.N, a.row_ptr, a.col, a.order, a.unit, a.Rt, a.Rtg, a.SF, a.SFf,
                        a.S);
@@ -563,22 +636,23 @@ template <int LM, bool TWO, bool SPLIT>
 hipError_t receiver_lm(const Args &a)
 {
     const int tiles = a.R / 16;
-    constexpr bool half = TWO || SPLIT;
+    constexpr bool half = TWO || SPLIT, F = receiver_values_f32(LM, 32, SPLIT);
     const bool es = a.N * tiles * (a.tb.d.UVs / 16) < kSplitTiles * (tiles == 1 ? 4 : 8);
     RecvLaunch l[2];
     const int n = recv_launches(tiles, half, es, l);
-    if (es)
-        return l[0].rt == 1 ? receiver_rt<LM, 1, 4, TWO, SPLIT, true>(a, l[0])
-                            : receiver_rt<LM, 2, 2, TWO, SPLIT, true, true>(a, l[0]);
+    if (tiles == 1)
+        return es ? receiver_rt<LM, 1, 4, TWO, SPLIT, true, true>(a, l[0])
+                  : receiver_rt<LM, 1, 4, TWO, SPLIT, true, false>(a, l[0]);
+    if (es) return receiver_rt<LM, 2, 2, TWO, SPLIT, F, true, true>(a, l[0]);
     for (int k = 0; k < n; ++k) {
         hipError_t e = hipErrorInvalidValue;
-        if (l[k].rt == 1) e = receiver_rt<LM, 1, 4, TWO, SPLIT, false>(a, l[k]);
         if constexpr (half) {
-            if (l[k].rt == 2) e = receiver_rt<LM, 2, 2, TWO, SPLIT, false>(a, l[k]);
+            if (l[k].rt == 1) e = receiver_rt<LM, 1, 4, TWO, SPLIT, F, false>(a, l[k]);
+            if (l[k].rt == 2) e = receiver_rt<LM, 2, 2, TWO, SPLIT, F, false>(a, l[k]);
         } else {
-            if (l[k].rt == 2) e = receiver_rt<LM, 2, 4, false, false, false>(a, l[k]);
-            if (l[k].rt == 3) e = receiver_rt<LM, 3, 2, false, false, false>(a, l[k]);
-            if (l[k].rt == 4) e = receiver_rt<LM, 4, 2, false, false, false>(a, l[k]);
+            if (l[k].rt == 2) e = receiver_rt<LM, 2, 4, false, false, F, false>(a, l[k]);
+            if (l[k].rt == 3) e = receiver_rt<LM, 3, 2, false, false, F, false>(a, l[k]);
+            if (l[k].rt == 4) e = receiver_rt<LM, 4, 2, false, false, F, false>(a, l[k]);
         }
         if (e != hipSuccess) return e;
     }
@@ -620,7 +694,7 @@ hipError_t launch_gather_probe_values(const Dims &d, int64_t N, int R, const int
     const int n = recv_launches(R / 16, false, false, l);
 #define CGTP_CASE(RTV, PTV)                                                                      \
     case RTV: {                                                                                  \
-        constexpr int waves = waves_for(false, RTV), chunk = 16 * PTV * waves;                   \
+        constexpr int waves = waves_for(false, RTV, 1), chunk = 16 * PTV * waves;                   \
         const int nchunks = (d.UV + chunk - 1) / chunk;                                          \
         const int64_t blocks = recv_blocks(N, (int64_t)l[k].groups * nchunks);                   \
         if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;                                  \

@@ -83,6 +83,21 @@ def test_receiver_values_cut_ranks(cg, lmax, R, n, slots):
     check_receiver(cg, lmax, R, n, slots)
 
 
+# The form on fp32 products at every rest of its reduction steps of four degrees (lmax 5, 6, 7, 8),
+# at the degrees of its one-step-shorter derivative sums (lmax 4, 8, 20), at the last degree, and on
+# both sides of its rule: a single rank tile against two, lmax 4 and 8 against 5 and 9, and with
+# per-block factors lmax 11, 12, 15 and 16. Ranks that no tile divides leave columns unwritten.
+F32_SHAPES = [(1, 100, 700), (4, 16, 30), (4, 112, 700), (5, 10, 1000), (6, 16, 40), (7, 15, 600),
+              (8, 64, 300), (8, 16, 30), (9, 16, 400), (11, 48, 120), (12, 32, 120), (15, 24, 90),
+              (16, 33, 90), (20, 12, 90), (24, 16, 60), (24, 40, 40)]
+
+
+@pytest.mark.parametrize("slots", ["one", "two", "blocks"])
+@pytest.mark.parametrize("lmax,R,n", F32_SHAPES)
+def test_receiver_values_f32(cg, lmax, R, n, slots):
+    check_receiver(cg, lmax, R, n, slots)
+
+
 def test_receiver_without_edges_among_others(cg):
     """Receivers with no edges give zeros in both forms; the others are unchanged."""
     for n, lmax, R in ((40, 5, 32), (900, 5, 64)):
