@@ -1148,6 +1148,10 @@ hipError_t launch_dense(const Tabs<float> &tb, int64_t rows, const float *H, flo
     return hipGetLastError();
 }
 
+// Workgroups below which the tiled sender takes smaller rank blocks: one per compute unit (one slot,
+// 120 nodes, R = 16, lmax 24: blocks of 16 ranks 51 us, of 8 or 4 38 us).
+constexpr int64_t kSenderBlocks = 256;
+
 // tiled: the value field in the tiles of k_receiver_values (planes is then not used).
 template <int LM>
 hipError_t sender_lm(const Tabs<float> &tb, int64_t B, int R, const float *H, float *SF,
@@ -1162,9 +1166,10 @@ hipError_t sender_lm(const Tabs<float> &tb, int64_t B, int R, const float *H, fl
     }
     const size_t fixed = 4 * (size_t)G::P + 4 * (size_t)G::KM * G::QB;
     int rb = pick_rb(tb.d, R, fixed, G::HR);
-    if (tiled) {  // a divisor of 16, three workgroups of four waves per compute unit
+    if (tiled) {  // a divisor of 16; three workgroups of four waves fit a compute unit
         rb = 16;
         while (rb > 4 && sizeof(float) * (fixed + rb * (size_t)G::HR) > (size_t)tb.d.lds_cu / 3) rb /= 2;
+        while (rb > 4 && B * (R / rb) < kSenderBlocks) rb /= 2;
         if (sizeof(float) * (fixed + rb * (size_t)G::HR) > (size_t)tb.d.lds_max)
             return hipErrorNotSupported;
     }

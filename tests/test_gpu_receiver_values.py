@@ -98,6 +98,12 @@ def test_receiver_values_f32(cg, lmax, R, n, slots):
     check_receiver(cg, lmax, R, n, slots)
 
 
+@pytest.mark.parametrize("n,lmax,R", [(17, 9, 16), (100, 12, 32), (130, 12, 32), (300, 9, 16)])
+def test_sender_rank_blocks(cg, n, lmax, R):
+    """The tiled sender's rank blocks of 4, 8 and 16 (fewer ranks with fewer nodes)."""
+    check_receiver(cg, lmax, R, n, "one")
+
+
 def test_receiver_without_edges_among_others(cg):
     """Receivers with no edges give zeros in both forms; the others are unchanged."""
     for n, lmax, R in ((40, 5, 32), (900, 5, 64)):
