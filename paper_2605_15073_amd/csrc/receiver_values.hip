@@ -637,13 +637,17 @@ hipError_t receiver_lm(const Args &a)
 {
     const int tiles = a.R / 16;
     constexpr bool half = TWO || SPLIT, F = receiver_values_f32(LM, 32, SPLIT);
-    const bool es = a.N * tiles * (a.tb.d.UVs / 16) < kSplitTiles * (tiles == 1 ? 4 : 8);
+    // Four waves of four degree groups take 100 KB of LDS, one workgroup per compute unit, and are
+    // slower than two that do not share the edges (20 nodes, lmax 24, R = 48: 110 against 55 us).
+    constexpr bool can_share = F || rt_groups(LM) < 4;
+    const bool es = (can_share || tiles == 1) && a.N * tiles * (a.tb.d.UVs / 16) < kSplitTiles * (tiles == 1 ? 4 : 8);
     RecvLaunch l[2];
     const int n = recv_launches(tiles, half, es, l);
     if (tiles == 1)
         return es ? receiver_rt<LM, 1, 4, TWO, SPLIT, true, true>(a, l[0])
                   : receiver_rt<LM, 1, 4, TWO, SPLIT, true, false>(a, l[0]);
-    if (es) return receiver_rt<LM, 2, 2, TWO, SPLIT, F, true, true>(a, l[0]);
+    if constexpr (can_share)
+        if (es) return receiver_rt<LM, 2, 2, TWO, SPLIT, F, true, true>(a, l[0]);
     for (int k = 0; k < n; ++k) {
         hipError_t e = hipErrorInvalidValue;
         if constexpr (half) {

@@ -98,6 +98,13 @@ def test_receiver_values_f32(cg, lmax, R, n, slots):
     check_receiver(cg, lmax, R, n, slots)
 
 
+@pytest.mark.parametrize("slots", ["one", "two", "blocks"])
+@pytest.mark.parametrize("lmax,R", [(24, 16), (24, 48)])
+def test_receiver_values_four_groups(cg, lmax, R, slots):
+    """Few nodes on both sides of the degree from which a workgroup's waves do not share edges."""
+    check_receiver(cg, lmax, R, 18, slots)
+
+
 @pytest.mark.parametrize("n,lmax,R", [(17, 9, 16), (100, 12, 32), (130, 12, 32), (300, 9, 16)])
 def test_sender_rank_blocks(cg, n, lmax, R):
     """The tiled sender's rank blocks of 4, 8 and 16 (fewer ranks with fewer nodes)."""
