@@ -411,7 +411,7 @@ template <>
 hipError_t launch_contract<float>(int64_t B, int Cin, int Cout, int K, bool kdeg, const float *W,
                                   int64_t w_sl, int64_t w_si, int64_t w_so, const float *X,
                                   int64_t x_sb, float *Y, int64_t y_sb, int64_t y_so, int64_t y_sk,
-                                  const float *scale, bool accumulate, hipStream_t s)
+                                  const float *scale, bool accumulate, hipStream_t s, int problems)
 {
     if (B == 0 || Cout == 0 || K == 0) return hipSuccess;
     if (x_sb < (int64_t)Cin * K) return hipErrorInvalidValue;
@@ -434,7 +434,8 @@ hipError_t launch_contract<float>(int64_t B, int Cin, int Cout, int K, bool kdeg
                            accumulate, nullptr, 0, 0, 0);
         return hipGetLastError();
     }
-    if (!scale && contract_rows_takes(B, Cin, Cout, K, w_sl, w_si, w_so, x_sb))
+    if (!scale &&
+        contract_rows_takes(B, Cin, Cout, K, w_sl, w_si, w_so, x_sb, accumulate, problems))
         return launch_contract_rows(B, Cin, Cout, K, W, w_sl, w_si, w_so, X, x_sb, Y, y_sb, y_so,
                                     y_sk, accumulate, nullptr, Pair2{}, s);
     const int64_t groups = (B + kTile - 1) / kTile;
@@ -495,7 +496,7 @@ hipError_t launch_contract_gather(int64_t B, int Cout, int K, const float *W, in
     if (nsrc > kMaxGather || xg.rows <= 0 || xg.rows % kCs != 0) return hipErrorNotSupported;
     const int Cin = nsrc * xg.rows;
     if (x_sb < (int64_t)xg.rows * K) return hipErrorInvalidValue;
-    if (contract_rows_takes(B, Cin, Cout, K, w_sl, w_si, w_so, x_sb))
+    if (contract_rows_takes(B, Cin, Cout, K, w_sl, w_si, w_so, x_sb, false, 1))
         return launch_contract_rows(B, Cin, Cout, K, W, w_sl, w_si, w_so, nullptr, x_sb, Y, y_sb,
                                     y_so, y_sk, false, &xg, Pair2{}, s);
     const int64_t groups = (B + kTile - 1) / kTile;
@@ -525,7 +526,7 @@ hipError_t launch_contract_pair(int64_t B, int Cin, int Cout, int K, const float
 {
     if (B == 0 || Cout == 0 || K == 0) return hipSuccess;
     if (x_sb < (int64_t)Cin * K) return hipErrorInvalidValue;
-    if (contract_rows_takes(B, Cin, Cout, K, w_sl, w_si, w_so, x_sb))
+    if (contract_rows_takes(B, Cin, Cout, K, w_sl, w_si, w_so, x_sb, false, 2))
         return launch_contract_rows(B, Cin, Cout, K, W0, w_sl, w_si, w_so, X0, x_sb, Y0, y_sb,
                                     y_so, y_sk, false, nullptr, Pair2{W1, X1, Y1, 0}, s);
     const int64_t groups = (B + kTile - 1) / kTile;
@@ -555,7 +556,7 @@ hipError_t launch_contract<double>(int64_t B, int Cin, int Cout, int K, bool kde
                                    const double *W, int64_t w_sl, int64_t w_si, int64_t w_so,
                                    const double *X, int64_t x_sb, double *Y, int64_t y_sb,
                                    int64_t y_so, int64_t y_sk, const double *scale,
-                                   bool accumulate, hipStream_t s)
+                                   bool accumulate, hipStream_t s, int)
 {
     int64_t total = B * (int64_t)Cout * K;
     if (total == 0) return hipSuccess;

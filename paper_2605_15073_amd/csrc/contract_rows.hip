@@ -265,11 +265,14 @@ int64_t block_count(int64_t B, int Cout, int K)
 }  // namespace
 
 bool contract_rows_takes(int64_t B, int Cin, int Cout, int K, int64_t w_sl, int64_t w_si,
-                         int64_t w_so, int64_t x_sb)
+                         int64_t w_so, int64_t x_sb, bool accumulate, int problems)
 {
     const int64_t blocks = block_count(B, Cout, K);
-    return K >= kNk && blocks >= kRowsMinBlocks && 2 * blocks <= 0x7fffffffLL && w_sl >= 0 &&
-           w_si >= 0 && w_so >= 0 &&
+    const bool large = (int64_t)Cin * Cout >= kRowsWork, wide = Cout >= kRowsWide;
+    if (K < kNk || blocks < kRowsMinBlocks) return false;
+    if (problems * blocks < 2 * kRowsMinBlocks && !large && !wide) return false;
+    if (accumulate && !wide && (Cout <= kRows || blocks < 2 * kRowsMinBlocks)) return false;
+    return 2 * blocks <= 0x7fffffffLL && w_sl >= 0 && w_si >= 0 && w_so >= 0 &&
            contract_rows_w_bytes(Cin, Cout, K, w_sl, w_si, w_so) < (int64_t)kOut &&
            4 * (kNodes * x_sb + (int64_t)(Cin + kSl) * K) < (int64_t)kOut;
 }

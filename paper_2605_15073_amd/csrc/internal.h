@@ -96,15 +96,15 @@ template <typename T>
 hipError_t launch_contract(int64_t B, int Cin, int Cout, int K, bool kdeg, const T *W,
                            int64_t w_sl, int64_t w_si, int64_t w_so, const T *X, int64_t x_sb,
                            T *Y, int64_t y_sb, int64_t y_so, int64_t y_sk, const T *scale,
-                           bool accumulate, hipStream_t s);
+                           bool accumulate, hipStream_t s, int problems = 1);
 template <>
 hipError_t launch_contract<float>(int64_t, int, int, int, bool, const float *, int64_t, int64_t,
                                   int64_t, const float *, int64_t, float *, int64_t, int64_t,
-                                  int64_t, const float *, bool, hipStream_t);
+                                  int64_t, const float *, bool, hipStream_t, int);
 template <>
 hipError_t launch_contract<double>(int64_t, int, int, int, bool, const double *, int64_t, int64_t,
                                    int64_t, const double *, int64_t, double *, int64_t, int64_t,
-                                   int64_t, const double *, bool, hipStream_t);
+                                   int64_t, const double *, bool, hipStream_t, int);
 
 // Edge coefficients of the values-only receiver (receiver_values.hip), R a multiple of 16. As
 // floats [E][L][R] (receiver_values_f32), from launch_contract's kdeg form; otherwise each value
@@ -169,14 +169,23 @@ hipError_t launch_contract_pair(int64_t B, int Cin, int Cout, int K, const float
                                 hipStream_t s);
 
 // The same contractions (kdeg false, no scale) in whole rows on bf16 triples
-// (contract_rows.hip), where contract_rows_takes says so. The rule looks at one problem's sizes
-// only, so that paired and single launches agree. xg: gathered input rows as
-// launch_contract_gather (X unused), or null; second.W: a second problem of the same sizes, or null.
-// Below 16 coefficients (one workgroup's share of k) most of a workgroup would idle; below
-// kRowsMinBlocks workgroups (one per compute unit) k_contract_mfma splits the work more finely
-// (300 nodes, lmax 3, 32 ranks: 80 workgroups against 19). At 256 workgroups a problem the
-// on-site call of 2,048 nodes, lmax 4, 64/64 takes 74 us here and 85 us there.
+// (contract_rows.hip), where contract_rows_takes says so. xg: gathered input rows as
+// launch_contract_gather (X unused), or null; second.W: a second problem of the same sizes, or
+// null. problems: how many problems of these sizes the call has when all of its outputs are
+// asked for, so that a launch of one agrees with the pair it would be half of.
+// Below 16 coefficients (one workgroup's share of k) most of a workgroup would idle. Below
+// kRowsMinBlocks workgroups a problem (one per compute unit) k_contract_mfma splits the work more
+// finely, and below twice as many over the call's problems too, unless a workgroup has enough to do
+// (kRowsWork products per coefficient and node, or kRowsWide outputs, several workgroups of which
+// share the inputs): one problem of 1,500 nodes, lmax 6, 376 workgroups, 32/32 12.5 us there and
+// 14.7 here; 512 nodes, lmax 8, 384 workgroups, 128/128 33.9 and 29.6; pairs of 256 workgroups,
+// 64/64, 2,048 nodes, lmax 4 26.5 and 21.5. Accumulating reads Y before each store, which pays
+// from kRowsWide outputs on, or above one workgroup's outputs with enough workgroups (24/24, 1,500
+// nodes, lmax 6 14.2 and 27.5 us; 64/64, 4,096 nodes 55 and 60; 96/96, 3,000 nodes 91 and 80;
+// 24/128, 1,500 nodes 40 and 34).
 constexpr int64_t kRowsMinBlocks = 256;
+constexpr int64_t kRowsWork = 3072;
+constexpr int kRowsWide = 128;
 inline int64_t contract_rows_w_bytes(int Cin, int Cout, int K, int64_t w_sl, int64_t w_si,
                                      int64_t w_so)
 {
@@ -185,7 +194,7 @@ inline int64_t contract_rows_w_bytes(int Cin, int Cout, int K, int64_t w_sl, int
     return 4 * ((L - 1) * w_sl + (Cin - 1) * w_si + (Cout - 1) * w_so + 1);
 }
 bool contract_rows_takes(int64_t B, int Cin, int Cout, int K, int64_t w_sl, int64_t w_si,
-                         int64_t w_so, int64_t x_sb);
+                         int64_t w_so, int64_t x_sb, bool accumulate, int problems);
 hipError_t launch_contract_rows(int64_t B, int Cin, int Cout, int K, const float *W, int64_t w_sl,
                                 int64_t w_si, int64_t w_so, const float *X, int64_t x_sb, float *Y,
                                 int64_t y_sb, int64_t y_so, int64_t y_sk, bool accumulate,

@@ -25,8 +25,10 @@ def cg():
     return lib
 
 
-# 256 workgroups (16 nodes x 16 k x 64 outputs) or more in each contraction
-SHAPES = [(3, 4090, 20, 9), (4, 2050, 33, 70), (6, 1030, 64, 40), (10, 515, 70, 96)]
+# 256 workgroups (16 nodes x 16 k x 64 outputs) or more in each contraction; the last three on both
+# sides of that line
+SHAPES = [(3, 4090, 20, 9), (4, 2050, 33, 70), (6, 1030, 64, 40), (10, 515, 70, 96),
+          (3, 4080, 16, 16), (3, 4081, 16, 16), (6, 500, 130, 20)]
 
 
 @pytest.mark.parametrize("lmax,n,C,R", SHAPES)
@@ -41,7 +43,12 @@ def test_contract_rows_onsite(cg, lmax, n, C, R):
         assert rel_err(a[rows], b) <= TOL_F32
 
 
-@pytest.mark.parametrize("lmax,n,C,R", [(4, 2050, 20, 24), (6, 1030, 64, 64), (3, 4090, 9, 32)])
+# both sides of the rules for one problem and for accumulating projections (R no multiple of 32):
+# below and from 512 workgroups, 64 and 65 outputs, 127 and 128, below and from 3,072 products
+@pytest.mark.parametrize("lmax,n,C,R", [(4, 2050, 20, 24), (6, 1030, 64, 64), (3, 4090, 9, 32),
+                                        (4, 4090, 64, 24), (4, 4090, 65, 24), (4, 2045, 65, 24),
+                                        (3, 4090, 127, 24), (3, 4090, 128, 24), (3, 4090, 47, 65),
+                                        (3, 4090, 48, 63), (3, 4090, 48, 64)])
 def test_contract_rows_general(cg, lmax, n, C, R):
     """Ranks of a multiple of 32 gather a sector's input rows, the others accumulate."""
     keys = ("A", "B", "A_flip", "B_flip", "U_A", "U_B", "U_out_even", "U_out_odd")
