@@ -985,7 +985,7 @@ __global__ __launch_bounds__(256) void k_analysis_mfma(Tabs<float> tb, int R, in
 // ------------------------------------------------------------- on-site grid stage
 
 template <int LM>
-__global__ __launch_bounds__(256) void k_onsite_mfma(Tabs<float> tb, int R, int rb,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LM <= 16 ? 3 : 1))) void k_onsite_mfma(Tabs<float> tb, int R, int rb,
                                                      const float *__restrict__ HA,
                                                      const float *__restrict__ HB,
                                                      float *__restrict__ Ta,
@@ -1298,12 +1298,13 @@ hipError_t launch_onsite_mfma(const Tabs<float> &tb, int64_t B, int R, const flo
 {
     if (B == 0) return hipSuccess;
     if (!default_grid(tb.d)) return hipErrorNotSupported;
-    static_assert(kOnsiteMfmaMinL == 21, "the degrees built");
+    static_assert(kOnsiteMfmaMinL == 15, "the degrees built");
     switch (tb.d.lmax) {
-    case 21: return onsite_lm<21>(tb, B, R, HA, HB, Ta, Tb, s);
-    case 22: return onsite_lm<22>(tb, B, R, HA, HB, Ta, Tb, s);
-    case 23: return onsite_lm<23>(tb, B, R, HA, HB, Ta, Tb, s);
-    case 24: return onsite_lm<24>(tb, B, R, HA, HB, Ta, Tb, s);
+#define CGTP_CASE(LMV) \
+    case LMV: return onsite_lm<LMV>(tb, B, R, HA, HB, Ta, Tb, s);
+        CGTP_CASE(15) CGTP_CASE(16) CGTP_CASE(17) CGTP_CASE(18) CGTP_CASE(19) CGTP_CASE(20)
+        CGTP_CASE(21) CGTP_CASE(22) CGTP_CASE(23) CGTP_CASE(24)
+#undef CGTP_CASE
     default: return hipErrorNotSupported;
     }
 }

@@ -336,9 +336,20 @@ hipError_t launch_sender_mfma(const Tabs<float> &tb, int64_t B, int R, const flo
 hipError_t launch_analysis_mfma(const Tabs<float> &tb, int64_t B, int R, const float *S,
                                 float *Ta, float *Tb, hipStream_t s, int mode = 0);
 // fp32 on-site grid stage on MFMA (fourier_mfma.hip), default grid only: the same
-// contract as launch_onsite_grid. Used from kOnsiteMfmaMinL up; below it the
-// register-resident folded kernel is faster.
-constexpr int kOnsiteMfmaMinL = 21;
+// contract as launch_onsite_grid. Below kOnsiteMfmaMinL the folded kernel is always the faster one,
+// above kOnsiteFoldedMaxL it is not built; between them it is, but for few (node, rank) rows: it
+// takes 256 / U of them a workgroup, this kernel up to 16 a workgroup of four waves, and finishes
+// a lone workgroup sooner (whole calls, this and the folded kernel: 8 rows lmax 15 33 and 38 us,
+// 16 30 and 48, 17 32 and 45, 20 39 and 59; 512 rows lmax 15 34 and 36, 1,024 39 and 37; 1,536
+// rows lmax 16 47 and 54, 2,048 63 and 56; 1,024 rows lmax 17 41 and 49, 20 59 and 64, 1,536 59
+// and 50, 97 and 67).
+constexpr int kOnsiteMfmaMinL = 15;
+inline bool onsite_mfma_takes(const Dims &d, int64_t rows)
+{
+    if (d.lmax < kOnsiteMfmaMinL) return false;
+    return d.lmax > kOnsiteFoldedMaxL ||
+           rows <= (d.lmax == kOnsiteMfmaMinL ? 512 : d.lmax == kOnsiteMfmaMinL + 1 ? 1536 : 1024);
+}
 hipError_t launch_onsite_mfma(const Tabs<float> &tb, int64_t B, int R, const float *HA,
                               const float *HB, float *Ta, float *Tb, hipStream_t s);
 

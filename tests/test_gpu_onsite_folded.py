@@ -1,5 +1,5 @@
 """The folded on-site kernels against the fp64 oracle over their degrees: every register and LDS
-shape (lmax 0 to 20; 21 takes the matrix-core kernel), rank blocks with remainders, and grids off
+shape (lmax 0 to 20; 21 takes the matrix-core kernel, and so do few rows from 15), rank blocks with remainders, and grids off
 the default one, whose Gauss-Legendre rows are not held in registers. fp32 bar of the other parity
 tests (2e-5 of the largest output)."""
 from __future__ import annotations
@@ -9,7 +9,7 @@ import pytest
 
 import oracle
 from paper_2605_15073_amd import inputs
-from tests.gpu_util import ONSITE_KEYS, TOL_F32, rel_err, run_onsite, to_dev
+from tests.gpu_util import ONSITE_KEYS, TOL_F32, rel_err, run_onsite, sample_rows, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -37,6 +37,23 @@ def test_folded_onsite(cg, lmax, R, grid):
     ref = oracle.onsite(lmax, d["A"], d["B"], d["U_A"], d["U_B"], d["U_out_even"], d["U_out_odd"])
     for a, b in zip(got, ref):
         assert rel_err(a, b) <= TOL_F32 or np.abs(b).max() == 0.0
+
+
+@pytest.mark.parametrize("lmax,n,R", [(15, 64, 8), (15, 57, 9), (16, 96, 16), (16, 140, 11),
+                                      (17, 64, 16), (17, 70, 15), (18, 41, 25), (19, 60, 18),
+                                      (20, 1, 1), (20, 128, 8),
+                                      (20, 79, 13)])
+def test_onsite_rows(cg, lmax, n, R):
+    """Degrees that the matrix-core kernel serves for few (node, rank) rows and the folded one for
+    more: the last row count of the one and the first of the other."""
+    d = inputs.onsite_inputs(n, lmax, 4, R, seed=540 + lmax, per_degree=True, distinct_out=True)
+    rows = sample_rows(n, 4, seed=lmax)
+    plan = cg.plan_create(lmax, 4, R)
+    got = run_onsite(cg, plan, to_dev(d, ONSITE_KEYS))
+    ref = oracle.onsite(lmax, d["A"][rows], d["B"][rows], d["U_A"], d["U_B"], d["U_out_even"],
+                        d["U_out_odd"])
+    for a, b in zip(got, ref):
+        assert rel_err(a[rows], b) <= TOL_F32
 
 
 @pytest.mark.parametrize("lmax,nu,extra", [(0, 2, 0), (3, 2, 0), (5, 3, 0), (9, 4, 0), (10, 4, 3),
