@@ -59,10 +59,11 @@ struct Tabs {
     const T *wdpt;  // [P][Ut] wq[u] * dp transposed
     const T *yc;    // [P] sqrt((2l+1)(l^2-m^2)/(2l-1)): (1-x^2) dPt_l^m/dx
                     //     = yc Pt_{l-1}^m - l x Pt_l^m
-    // Azimuths of the folded on-site kernels: V4 = 4 Q >= V points phi_v = 2 pi (v + 1/2) / V4,
-    // as exact as the grid's own, of which the first Q give the others by reflection
-    const T *qf;    // [Q][M] real Fourier factors at phi_v, v < Q (columns as q)
-    const T *qdf;   // [Q][M] their phi-derivative weights: column LM + k holds k qf[v][LM + k],
+    // Azimuths of the folded on-site kernels: V4 = 4 Q >= V equispaced points (fold_quads), as
+    // exact as the grid's own, of which the fold_rows first give the others by reflection:
+    // phi_v = 2 pi (v + 1/2) / V4, v < Q, or (fold_whole) 2 pi v / V4, v <= Q
+    const T *qf;    // [rows][M] real Fourier factors at phi_v (columns as q)
+    const T *qdf;   // [rows][M] their phi-derivative weights: column LM + k holds k qf[v][LM + k],
                     // column LM - k holds -k qf[v][LM - k] (k >= 1), column LM zero
     const T *wpf;   // [P][Ut] w_u (2 pi / V4) * p transposed
     const T *ysyn;  // [KP][3 UVs] for lmax <= kDenseSynthMaxL (else empty): row k = (l, m),
@@ -77,7 +78,31 @@ struct Tabs {
 // a row are then one product of its coefficients with that table).
 constexpr int kDenseSynthMaxL = 6;
 
-inline int fold_quads(const Dims &d) { return (d.V + 3) / 4; }  // Q
+// Whether the folded azimuths start at 0 (a row more: 0 and pi / 2 are their own reflections and
+// count half) instead of at half a step. At low degrees the few factors' rounding does not average
+// out, and a set's error depends on which of them are exact: where half steps were further from 64
+// bits than the grid's own azimuths, whole steps or one more quadruple (fold_quads) are taken.
+// Error of the grid stage over that of the grid's azimuths, half steps and the set taken (fp32 with
+// FMA, emulated): two operands, lmax 1 0.88, 2 1.21 and 0.91, 3 0.99, 4 0.89; three, lmax 1 1.16
+// and 0.72, 2 1.15 and 0.99, 3 0.94, 4 1.09 and 0.91, 5 0.97; four, lmax 1 1.04 and 0.61, 2 1.12
+// and 0.97, 3 1.05 and 0.91, 4 0.99, 5 0.96; above, 0.83 to 0.98.
+constexpr int kFoldWholeMaxL = 4;
+inline bool fold_whole(const Dims &d)
+{
+    switch (d.lmax) {
+    case 1: return d.V > 4;
+    case 2: return d.V < 8 || d.V > 10;
+    case 3: return d.V > 13;
+    case 4: return d.V > 13 && d.V < 21;
+    default: return false;
+    }
+}
+inline int fold_quads(const Dims &d)  // Q
+{
+    if (d.lmax == 2 && d.V >= 8 && d.V <= 10) return 4;
+    return (d.V + 3) / 4 + (fold_whole(d) && d.lmax >= 3 ? 1 : 0);
+}
+inline int fold_rows(const Dims &d) { return fold_quads(d) + (fold_whole(d) ? 1 : 0); }
 
 // Number of T elements of each table region, in the order of Tabs.
 size_t table_elems(const Dims &d);

@@ -6,7 +6,8 @@
 // time. The integrand needs V >= 3 lmax + 1 equispaced azimuths wherever they start, so the
 // sweep takes V4 = 4 Q of them at half steps, phi_v = 2 pi (v + 1/2) / V4: phi, -phi, pi - phi
 // and pi + phi then are four different points whose cos(m phi) and sin(m phi) differ in sign
-// only, by the parity of m. Four partial sums per field (cosine and sine, even and odd m)
+// only, by the parity of m (at low degrees whole steps, fold_whole, which are more accurate
+// there: a step more, whose ends count half). Four partial sums per field (cosine and sine, even and odd m)
 // give its values (Eq. struct-tildeA) at all four, where the product (Eq. struct-S) and the
 // surface curl (Eq. poisson-S2-x) are formed, and four signed sums of those go back into the
 // Fourier analysis (Eq. struct-Tmu): a quarter of the products of a plain sweep, half of those
@@ -155,16 +156,30 @@ constexpr int default_ut(int lm, int nu)
     return ((u < 1 ? 1 : u) + 3) / 4 * 4;
 }
 
+// Whole steps (fold_whole): the first and last step's four points are two, each counted twice, so
+// one factor of the product counts half there (its partial sums, exactly: the products and their
+// sums keep their rounding).
+template <int LM>
+__device__ __forceinline__ void halve_ends(Quad &a, int step, int steps, bool whole)
+{
+    if (LM < 1 || LM > kFoldWholeMaxL) return;  // always half steps
+    const float w = whole && (step == 0 || step == steps - 1) ? 0.5f : 1.f;
+    a.ce *= w;
+    a.co *= w;
+    a.se *= w;
+    a.so *= w;
+}
+
 // Azimuth sweep of one row at latitude u for the Gaunt product (Eq. struct-S): synthesise
 // A from FA and B from FB at the four points of each quadrant step and add the Fourier analysis
 // (Eq. struct-Tmu) of A B into T. qs: the plan's qf, passed down from a read-only kernel argument
 // so that each row is read with scalar loads.
 template <int LM>
 __device__ __forceinline__ void sweep_product(const float *FA, const float *FB, const float *qs,
-                                              int quads, float *T)
+                                              int steps, bool whole, float *T)
 {
     constexpr int M = 2 * LM + 1;
-    for (int v = 0; v < quads; ++v) {
+    for (int v = 0; v < steps; ++v) {
         const float *qr = qs + v * M;
         Quad a{FA[LM], 0.f, 0.f, 0.f}, c{FB[LM], 0.f, 0.f, 0.f};
 #pragma unroll
@@ -172,6 +187,7 @@ __device__ __forceinline__ void sweep_product(const float *FA, const float *FB, 
             quad_add(a, k, qr[LM + k], FA[LM + k], qr[LM - k], FA[LM - k]);
             quad_add(c, k, qr[LM + k], FB[LM + k], qr[LM - k], FB[LM - k]);
         }
+        halve_ends<LM>(a, v, steps, whole);
         float va[4], vc[4];
         quad_values(a, va);
         quad_values(c, vc);
@@ -186,10 +202,10 @@ __device__ __forceinline__ void sweep_product(const float *FA, const float *FB, 
 template <int LM>
 __device__ __forceinline__ void sweep_curl(const float *FA, const float *FxA, const float *FB,
                                            const float *FxB, const float *qs, const float *qds,
-                                           int quads, float *T)
+                                           int steps, bool whole, float *T)
 {
     constexpr int M = 2 * LM + 1;
-    for (int v = 0; v < quads; ++v) {
+    for (int v = 0; v < steps; ++v) {
         const float *qr = qs + v * M, *qdr = qds + v * M;
         Quad ax{FxA[LM], 0.f, 0.f, 0.f}, ap{0.f, 0.f, 0.f, 0.f};
         Quad cx{FxB[LM], 0.f, 0.f, 0.f}, cp{0.f, 0.f, 0.f, 0.f};
@@ -202,6 +218,8 @@ __device__ __forceinline__ void sweep_curl(const float *FA, const float *FxA, co
             quad_add(cx, k, cs, FxB[LM + k], sn, FxB[LM - k]);
             quad_add(cp, k, kc, FB[LM - k], mks, FB[LM + k]);
         }
+        halve_ends<LM>(ap, v, steps, whole);
+        halve_ends<LM>(ax, v, steps, whole);
         float vx[4], vp[4], sb[4];
         quad_values(ap, vp);
         quad_values(cx, vx);
@@ -225,7 +243,7 @@ constexpr int folded_waves(int lm) { return lm >= 15 ? 2 : lm >= 11 ? 3 : lm >= 
 // traffic in the sweep).
 template <int LM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(folded_waves(LM))))
-void k_onsite_folded(Tabs<float> tb, int R, int rb, int quads,
+void k_onsite_folded(Tabs<float> tb, int R, int rb, int steps, bool whole,
                      const float *__restrict__ qg, const float *__restrict__ qdg,
                      const float *__restrict__ HA, const float *__restrict__ HB,
                      float *__restrict__ Ta, float *__restrict__ Tb)
@@ -244,12 +262,12 @@ void k_onsite_folded(Tabs<float> tb, int R, int rb, int quads,
     const int64_t b = blockIdx.x / nrb;
     const int r0 = (int)(blockIdx.x - b * nrb) * rb;
     const int nr = (R - r0 < rb) ? (R - r0) : rb;
+    const int64_t row0 = (b * R + r0) * (int64_t)K;
     for (int k = threadIdx.x; k < U * P; k += blockDim.x) {
         const int uu = k / P, o = uu * PS + k - uu * P;
         ps[o] = tb.p[k];
         dps[o] = tb.dp[k];
     }
-    const int64_t row0 = (b * R + r0) * (int64_t)K;
     for (int k = threadIdx.x; k < nr * K; k += blockDim.x) {
         Hs[k] = HA[row0 + k];
         Hs[rb * K + k] = HB[row0 + k];
@@ -288,14 +306,14 @@ void k_onsite_folded(Tabs<float> tb, int R, int rb, int quads,
 #pragma unroll
     for (int mi = 0; mi < M; ++mi) T[mi] = 0.f;
     if (active) {
-        sweep_curl<LM>(FA, FxA, FB, FxB, qg, qdg, quads, T);
+        sweep_curl<LM>(FA, FxA, FB, FxB, qg, qdg, steps, whole, T);
         store_fourier<LM>(Tm, ts, q, u, U, T);
     }
     __syncthreads();
     gl_analyse<LM, default_ut(LM, 2)>(tb, Tm, nr, Tb + row0);
 #pragma unroll
     for (int mi = 0; mi < M; ++mi) T[mi] = 0.f;
-    if (active) sweep_product<LM>(FA, FB, qg, quads, T);
+    if (active) sweep_product<LM>(FA, FB, qg, steps, whole, T);
     __syncthreads();  // the curl's Fourier rows are read
     if (active) store_fourier<LM>(Tm, ts, q, u, U, T);
     __syncthreads();
@@ -325,7 +343,7 @@ hipError_t launch_folded(const Tabs<float> &tb, int64_t B, int R, const float *H
     const int threads = (rb * U + 63) / 64 * 64;
     const int64_t blocks = B * ((R + rb - 1) / rb);
     hipLaunchKernelGGL((k_onsite_folded<LM>), dim3((unsigned)blocks), dim3(threads), lds, s, tb, R,
-                       rb, fold_quads(tb.d), tb.qf, tb.qdf, HA, HB, Ta, Tb);
+                       rb, fold_rows(tb.d), fold_whole(tb.d), tb.qf, tb.qdf, HA, HB, Ta, Tb);
     return hipGetLastError();
 }
 
@@ -337,7 +355,7 @@ hipError_t launch_folded(const Tabs<float> &tb, int64_t B, int R, const float *H
 // k_onsite_folded.
 template <int LM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LM == 11 || LM == 12 ? 3 : 1)))
-void k_onsite_split(Tabs<float> tb, int R, int rb, int quads, const float *__restrict__ qg,
+void k_onsite_split(Tabs<float> tb, int R, int rb, int steps, bool whole, const float *__restrict__ qg,
                     const float *__restrict__ qdg, const float *__restrict__ HA,
                     const float *__restrict__ HB, const float *__restrict__ HAc,
                     const float *__restrict__ HBc, float *__restrict__ Ta,
@@ -399,7 +417,7 @@ void k_onsite_split(Tabs<float> tb, int R, int rb, int quads, const float *__res
                 FB[mi] = f2;
                 FxB[mi] = g2;
             }
-            sweep_curl<LM>(FA, FxA, FB, FxB, qg, qdg, quads, TB);
+            sweep_curl<LM>(FA, FxA, FB, FxB, qg, qdg, steps, whole, TB);
         }
         {
             const float *h1 = Hs + q * K, *h2 = Hs + (rb + q) * K;
@@ -417,7 +435,7 @@ void k_onsite_split(Tabs<float> tb, int R, int rb, int quads, const float *__res
                 FA[mi] = f1;
                 FB[mi] = f2;
             }
-            sweep_product<LM>(FA, FB, qg, quads, TA);
+            sweep_product<LM>(FA, FB, qg, steps, whole, TA);
         }
     }
     __syncthreads();  // every thread has its Fourier rows: Hs is free for Tm
@@ -446,7 +464,8 @@ hipError_t launch_split(const Tabs<float> &tb, int64_t B, int R, const float *HA
     const int threads = (rb * U + 63) / 64 * 64;
     const int64_t blocks = B * ((R + rb - 1) / rb);
     hipLaunchKernelGGL((k_onsite_split<LM>), dim3((unsigned)blocks), dim3(threads), lds(rb), s,
-                       tb, R, rb, fold_quads(tb.d), tb.qf, tb.qdf, HA, HB, HAc, HBc, Ta, Tb);
+                       tb, R, rb, fold_rows(tb.d), fold_whole(tb.d), tb.qf, tb.qdf, HA, HB, HAc,
+                       HBc, Ta, Tb);
     return hipGetLastError();
 }
 
@@ -457,7 +476,8 @@ hipError_t launch_split(const Tabs<float> &tb, int64_t B, int R, const float *HA
 // the product in registers. The Gauss-Legendre analysis across u (Eq. struct-Tlm)
 // goes through LDS. The grid (U, V) is the plan's, exact for the (NU + 1) lmax integrand.
 template <int LM, int NU>
-__global__ __launch_bounds__(256) void k_nbody_folded(Tabs<float> tb, int R, int rb, int quads,
+__global__ __launch_bounds__(256) void k_nbody_folded(Tabs<float> tb, int R, int rb, int steps,
+                                                      bool whole,
                                                       const float *__restrict__ qg,
                                                       NbodyOperands<float> H,
                                                       float *__restrict__ Tout)
@@ -509,7 +529,7 @@ __global__ __launch_bounds__(256) void k_nbody_folded(Tabs<float> tb, int R, int
     }
     __syncthreads();  // every thread has its coefficients: Hs is free for Tm
     if (active) {
-        for (int v = 0; v < quads; ++v) {
+        for (int v = 0; v < steps; ++v) {
             const float *qr = qg + v * M;
             float s[4];
 #pragma unroll
@@ -518,6 +538,7 @@ __global__ __launch_bounds__(256) void k_nbody_folded(Tabs<float> tb, int R, int
 #pragma unroll
                 for (int k = 1; k <= LM; ++k)
                     quad_add(a, k, qr[LM + k], F[t][LM + k], qr[LM - k], F[t][LM - k]);
+                if (t == 0) halve_ends<LM>(a, v, steps, whole);
                 float x[4];
                 quad_values(a, x);
 #pragma unroll
@@ -546,7 +567,7 @@ hipError_t launch_nbody_folded_lm(const Tabs<float> &tb, int64_t B, int R,
     const int64_t blocks = B * ((R + rb - 1) / rb);
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     hipLaunchKernelGGL((k_nbody_folded<LM, NU>), dim3((unsigned)blocks), dim3(threads), lds, s, tb,
-                       R, rb, fold_quads(tb.d), tb.qf, H, Tout);
+                       R, rb, fold_rows(tb.d), fold_whole(tb.d), tb.qf, H, Tout);
     return hipGetLastError();
 }
 

@@ -168,9 +168,9 @@ static void region_sizes(const Dims &d, size_t *n)
     n[17] = (size_t)d.P * ut;   // wpt
     n[18] = d.P;                // yc
     n[19] = d.lmax <= kDenseSynthMaxL ? (size_t)(d.K + 3) / 4 * 4 * 3 * d.UVs : 0;  // ysyn
-    n[20] = (size_t)fold_quads(d) * d.M;  // qf
+    n[20] = (size_t)fold_rows(d) * d.M;  // qf
     n[21] = (size_t)d.P * ut;   // wdpt
-    n[22] = (size_t)fold_quads(d) * d.M;  // qdf
+    n[22] = (size_t)fold_rows(d) * d.M;  // qdf
     n[23] = (size_t)d.P * ut;   // wpf
 }
 
@@ -245,14 +245,22 @@ void fill_tables(const Dims &d, double *h)
     // their Fourier factors (real basis: d/dphi maps cos(k phi) to -k sin(k phi) and sin(k phi)
     // to k cos(k phi))
     const int quads = fold_quads(d);
-    for (int v = 0; v < quads; ++v) {
-        const double ph = 2.0 * kPi * (v + 0.5) / (4.0 * quads);
+    // cos and sin of i quarter turns / (2 quads), exact at the multiples of a quarter turn
+    auto turn = [&](bool sine, int64_t i) {
+        i %= 8 * (int64_t)quads;
+        static const double quarter[4] = {1.0, 0.0, -1.0, 0.0};  // cos
+        if (i % (2 * quads) == 0) return quarter[(i / (2 * quads) + (sine ? 3 : 0)) % 4];
+        const double a = kPi * (double)i / (4.0 * quads);
+        return sine ? std::sin(a) : std::cos(a);
+    };
+    for (int v = 0; v < fold_rows(d); ++v) {
+        const int i = fold_whole(d) ? 2 * v : 2 * v + 1;  // phi_v = 2 pi i / (8 quads)
         double *qv = h + off[20] + (size_t)v * d.M + d.lmax;
         double *dv = h + off[22] + (size_t)v * d.M + d.lmax;
         qv[0] = 1.0;
         for (int k = 1; k <= d.lmax; ++k) {
-            qv[k] = std::sqrt(2.0) * std::cos(k * ph);
-            qv[-k] = std::sqrt(2.0) * std::sin(k * ph);
+            qv[k] = std::sqrt(2.0) * turn(false, (int64_t)k * i);
+            qv[-k] = std::sqrt(2.0) * turn(true, (int64_t)k * i);
             dv[k] = k * qv[k];
             dv[-k] = -k * qv[-k];
         }
