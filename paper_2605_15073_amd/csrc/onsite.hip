@@ -233,6 +233,14 @@ __device__ __forceinline__ void sweep_curl(const float *FA, const float *FxA, co
     }
 }
 
+// Degree 0 on one node and one quadruple of azimuths: a field is its one value there, so a thread
+// takes a rank from coefficient to coefficient, with the sweeps' arithmetic and without their LDS
+// passes (20,000 nodes, 16 ranks, whole call 28 -> 25 us; on the former kernels 25).
+__device__ __forceinline__ float analyse_constant(const Tabs<float> &tb, float v)
+{
+    return tb.wpf[0] * (4.f * v);
+}
+
 // Waves per SIMD of k_onsite_folded: what the registers of four coefficient rows and one Fourier
 // row leave room for (unforced, the scheduler takes a wave's registers more at lmax 8 and 9 and
 // the grid stage 176 instead of 149 us, 2,048 nodes, 64 ranks).
@@ -263,6 +271,15 @@ void k_onsite_folded(Tabs<float> tb, int R, int rb, int steps, bool whole,
     const int r0 = (int)(blockIdx.x - b * nrb) * rb;
     const int nr = (R - r0 < rb) ? (R - r0) : rb;
     const int64_t row0 = (b * R + r0) * (int64_t)K;
+    if (LM == 0 && U == 1 && steps == 1) {
+        if ((int)threadIdx.x < nr) {
+            const float h1 = HA[row0 + threadIdx.x], h2 = HB[row0 + threadIdx.x];
+            const float p = tb.p[0], dp = tb.dp[0];
+            Ta[row0 + threadIdx.x] = analyse_constant(tb, (p * h1) * (p * h2));
+            Tb[row0 + threadIdx.x] = analyse_constant(tb, 0.f * (dp * h2) - (dp * h1) * 0.f);
+        }
+        return;
+    }
     for (int k = threadIdx.x; k < U * P; k += blockDim.x) {
         const int uu = k / P, o = uu * PS + k - uu * P;
         ps[o] = tb.p[k];
@@ -381,6 +398,16 @@ void k_onsite_split(Tabs<float> tb, int R, int rb, int steps, bool whole, const 
         dps[o] = tb.dp[k];
     }
     const int64_t row0 = (b * R + r0) * (int64_t)K;
+    if (LM == 0 && U == 1 && steps == 1) {
+        if ((int)threadIdx.x < nr) {
+            const float h1 = HA[row0 + threadIdx.x], h2 = HB[row0 + threadIdx.x];
+            const float c1 = HAc[row0 + threadIdx.x], c2 = HBc[row0 + threadIdx.x];
+            const float p = tb.p[0], dp = tb.dp[0];
+            Ta[row0 + threadIdx.x] = analyse_constant(tb, (p * h1) * (p * h2));
+            Tb[row0 + threadIdx.x] = analyse_constant(tb, 0.f * (dp * c2) - (dp * c1) * 0.f);
+        }
+        return;
+    }
     for (int k = threadIdx.x; k < nr * K; k += blockDim.x) {
         Hs[k] = HA[row0 + k];
         Hs[rb * K + k] = HB[row0 + k];
@@ -500,6 +527,15 @@ __global__ __launch_bounds__(256) void k_nbody_folded(Tabs<float> tb, int R, int
         ps[uu * PS + k - uu * P] = tb.p[k];
     }
     const int64_t row0 = (b * R + r0) * (int64_t)K;
+    if (LM == 0 && U == 1 && steps == 1) {
+        if ((int)threadIdx.x < nr) {
+            float v = 1.f;
+#pragma unroll
+            for (int t = 0; t < NU; ++t) v *= tb.p[0] * H.h[t][row0 + threadIdx.x];
+            Tout[row0 + threadIdx.x] = analyse_constant(tb, v);
+        }
+        return;
+    }
 #pragma unroll
     for (int t = 0; t < NU; ++t) {
         const float *h = H.h[t] + row0;

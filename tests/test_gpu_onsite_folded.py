@@ -56,6 +56,17 @@ def test_onsite_rows(cg, lmax, n, R):
         assert rel_err(a[rows], b) <= TOL_F32
 
 
+@pytest.mark.parametrize("n,R,extra", [(1, 1, 0), (5, 300, 0), (5, 300, 4), (700, 17, 0)])
+def test_degree_zero(cg, n, R, extra):
+    """The constant product: even output against the oracle, odd output zero."""
+    d = inputs.onsite_inputs(n, 0, 4, R, seed=580, per_degree=True, distinct_out=True)
+    kw = dict(n_theta=1 + extra, n_phi=1 + extra) if extra else {}
+    got = run_onsite(cg, cg.plan_create(0, 4, R, **kw), to_dev(d, ONSITE_KEYS))
+    ref = oracle.onsite(0, d["A"], d["B"], d["U_A"], d["U_B"], d["U_out_even"], d["U_out_odd"])
+    assert rel_err(got[0], ref[0]) <= TOL_F32
+    assert float(got[1].abs().max()) == 0.0 and np.abs(ref[1]).max() == 0.0
+
+
 @pytest.mark.parametrize("lmax,nu,extra", [(0, 2, 0), (3, 2, 0), (5, 3, 0), (9, 4, 0), (10, 4, 3),
                                            (4, 3, 6)])
 def test_folded_nbody(cg, lmax, nu, extra):
