@@ -38,6 +38,10 @@
  *    channel and r the CP rank.
  *  - The caller owns every buffer it passes. Inputs are read only. Outputs are
  *    fully overwritten (no accumulation into existing contents).
+ *  - fp32 plans form some products from three bf16 parts of each operand, 24 bits together. Edge
+ *    coefficients (sum_n U_E R) below 2^-109 in magnitude are held to within 2^-134, and an
+ *    infinite one gives NaN where fp32 sums might give infinity; all other operands have the
+ *    range and precision of fp32.
  *  - Calls are asynchronous on `stream` (a hipStream_t cast to void*, NULL for
  *    the default stream): they return after enqueueing the kernels.
  *  - Every function returns CGTP_OK (0) or a negative status; none aborts or

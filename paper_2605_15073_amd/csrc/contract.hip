@@ -222,6 +222,16 @@ constexpr int kSB = 34;          // LDS row stride of a staged X row (kCk * kLG 
 constexpr int kSW = kTile + 16;  // LDS row stride of Ws: lane groups of a half-wave apart
 constexpr int kNX = kTile * kCk * kLG / kThreadsC;  // staged elements per thread and slice
 
+// Finite values above bf16's largest, which would round to infinity, as that (the parts that follow
+// hold the rest); NaN stays NaN.
+__device__ __forceinline__ float2_t saturate(float2_t v)
+{
+    constexpr float top = 0x1.fep127f;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) v[k] = v[k] > top ? top : v[k] < -top ? -top : v[k];
+    return v;
+}
+
 // PARTS: the output as bf16 triples in the slot vectors of the values-only receiver,
 // Yp [B][rtiles][3][ndg][16 ranks][8 degrees], ranks r0 + o (zeros for o in [Cout, oend)): a
 // lane's kLG = 4 degrees of one rank are half a slot vector, one 8-byte store per part.
@@ -341,8 +351,8 @@ __global__ __launch_bounds__(kThreadsC, 4) void k_contract_kdeg(
 #pragma unroll
                     for (int q = 0; q < 3; ++q) {
                         const uint2_t w = {
-                            __builtin_bit_cast(unsigned, __builtin_convertvector(lo, bf2_t)),
-                            __builtin_bit_cast(unsigned, __builtin_convertvector(hi, bf2_t))};
+                            __builtin_bit_cast(unsigned, __builtin_convertvector(saturate(lo), bf2_t)),
+                            __builtin_bit_cast(unsigned, __builtin_convertvector(saturate(hi), bf2_t))};
                         y[q * ndg * 16 * vw] = w;
                         lo[0] -= __builtin_bit_cast(float, w[0] << 16);
                         lo[1] -= __builtin_bit_cast(float, w[0] & 0xffff0000u);

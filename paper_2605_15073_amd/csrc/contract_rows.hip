@@ -9,17 +9,22 @@
 //
 // A k needs operands of its own, which the fp32 matrix instructions pay for (every layout of
 // this kind measured slower on them). The products therefore run on 16x16x32 bf16 instructions,
-// 16 times faster, over exact three-part operands x = h + m + l (24 bits of significand): hh, hm,
-// mh, mm, hl, lh, accumulated in fp32; what is left out is below 2^-24 of the term. X is split
-// once per workgroup into LDS, in the order the lanes read it; a wave splits the weights of its
-// own 16 outputs in registers, once per degree and slice, loaded a degree ahead.
+// 16 times faster, over three-part operands x = h + m + l (24 bits of significand): hh, hm, mh, mm,
+// hl, lh, accumulated in fp32; what is left out is below 2^-24 of the term. The parts are exact
+// where the third is no smaller than bf16's smallest step, 2^-133, so from 2^-109 on, and up to
+// bf16's largest value; an infinite operand has none. A workgroup that meets a node's row or a
+// group of weights outside that range (parts_lose) forms its sums in plain fp32 instead, so that
+// tiny, huge and infinite operands give what k_contract_mfma gives, whichever of the two a size
+// selects (the check costs 1 to 3% of a call). X is split once per workgroup into LDS, in the order
+// the lanes read it; a wave splits the weights of its own 16 outputs in registers, once per degree
+// and slice, loaded a degree ahead.
 //
 // Measured, k_contract_mfma and this kernel: on-site calls of 4,096 nodes, lmax 12, 128 channels
-// and ranks 2.96 -> 2.47 ms; 2,048 nodes, lmax 4, 64/64 85 -> 74 us; 1,237 nodes, lmax 17, 72/56
-// 1.02 -> 0.91 ms; edge fields, 1,000 atoms, lmax 6, 64/64 10.8 -> 10.1 ms; 10^4 atoms, lmax 6,
+// and ranks 2.96 -> 2.48 ms; 2,048 nodes, lmax 4, 64/64 85 -> 75 us; 1,237 nodes, lmax 17, 72/56
+// 1.02 -> 0.92 ms; edge fields, 1,000 atoms, lmax 6, 64/64 10.8 -> 10.1 ms; 10^4 atoms, lmax 6,
 // 128/128 9.79 -> 9.54 ms. Errors of the whole calls against 64 bits fall (lmax 12 3.9e-7 -> 3.1e-7:
 // a slice of 32 inputs is one instruction's sum). Bound by latency at three waves per SIMD, which
-// registers (153) and LDS (49 KB a workgroup) set.
+// registers (155) and LDS (49 KB a workgroup) set.
 #include "internal.h"
 
 namespace cgtp {
@@ -73,6 +78,20 @@ __device__ __forceinline__ void split8(const float *x, uint4_t (&part)[3])
     }
 }
 
+// Whether parts lose bits of operands whose largest magnitude is m (a maximum that skips NaN, which
+// parts propagate): all of them below the range (one inside dwarfs what the others lose, 2^-134
+// each), or one above it.
+__device__ __forceinline__ bool parts_lose(float m)
+{
+    return (m < 0x1p-104f && m != 0.f) || m > 0x1.fep127f;
+}
+
+// The largest of m, |a| and |b| (fmaxf would first quieten each operand, an instruction of its own).
+__device__ __forceinline__ void max_abs(float &m, float a, float b)
+{
+    asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(m) : "v"(a), "v"(b));
+}
+
 // Orders a wave's LDS writes before its other lanes' reads (a wave's LDS operations complete in
 // order).
 __device__ __forceinline__ void wave_sync()
@@ -92,6 +111,7 @@ __global__ __launch_bounds__(kThreadsR, 3) void k_contract_rows(
     Pair2 second)
 {
     __shared__ uint4_t sh[kNk * kStride];
+    __shared__ int plain;  // some operand is outside the range of parts
     // Block b runs on XCD b % 8: the blocks of a node group, which share lines of X and Y, get
     // consecutive ids on one XCD.
     const int64_t nblk = gridDim.x, per = nblk / 8, rem = nblk % 8;
@@ -161,11 +181,16 @@ __global__ __launch_bounds__(kThreadsR, 3) void k_contract_rows(
     float4_t acc[kNk];
 #pragma unroll
     for (int k = 0; k < kNk; ++k) acc[k] = float4_t{0.f, 0.f, 0.f, 0.f};
+    float xmax = 0.f;   // of this thread's node and k, all inputs
+    bool lose = false;  // its weights, group by group
 
+    if (tid == 0) plain = 0;
     fetch(0);
     wfetch(0, l0);
     for (int i0 = 0; i0 < Cin; i0 += kSl) {
         __syncthreads();  // the previous slice is consumed
+#pragma unroll
+        for (int i = 0; i < kSl; i += 2) max_abs(xmax, xr[i], xr[i + 1]);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             uint4_t part[3];
@@ -184,6 +209,10 @@ __global__ __launch_bounds__(kThreadsR, 3) void k_contract_rows(
         for (int k = 0; k < kNk; ++k) {
             if (k == kb) {
                 split8(wr, wp);
+                float wmax = 0.f;
+#pragma unroll
+                for (int e = 0; e < 8; e += 2) max_abs(wmax, wr[e], wr[e + 1]);
+                lose |= parts_lose(wmax);
                 ++l;
                 kb = (l + 1) * (l + 1) - k0;
                 const bool more = kb < nk;  // else the next slice's first degree (zeros past Cin)
@@ -208,8 +237,27 @@ __global__ __launch_bounds__(kThreadsR, 3) void k_contract_rows(
         }
     }
 
+    if (lose || parts_lose(xmax)) plain = 1;
+    __syncthreads();  // (also: the last slice is consumed)
+    if (plain) {
+        const int ob = o0 + 16 * wave + 4 * g;
+#pragma unroll
+        for (int k = 0; k < kNk; ++k) {
+            acc[k] = float4_t{0.f, 0.f, 0.f, 0.f};
+            if (k >= nk || n >= nb) continue;
+            int lk = l0;
+            while ((lk + 1) * (lk + 1) <= k0 + k) ++lk;
+            for (int i = 0; i < Cin; ++i) {
+                const int src = GATHER ? i / xg.rows : 0, ii = GATHER ? i - src * xg.rows : i;
+                const float x = (GATHER ? xg.base[src] : X)[(b0 + n) * x_sb + (int64_t)ii * K + k0 + k];
+                const float *w = W + (int64_t)lk * w_sl + (int64_t)i * w_si;
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (ob + j < Cout) acc[k][j] += w[(int64_t)(ob + j) * w_so] * x;
+            }
+        }
+    }
     // D[o = 4 g + j][b = n] of each k: rows (b, o) of 16 k leave through LDS, two j at a time
-    __syncthreads();
     float *ys = reinterpret_cast<float *>(sh) + wave * (8 * kNodes * kYs);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {

@@ -15,8 +15,10 @@
 // on this chip they do not overlap vector instructions of other waves (16x16x4 fp32 products
 // and FMAs that take 229 and 296 us apart take 510 us together), so a receiver on them paid the
 // sum of its matrix and vector time. The 16x16x32 bf16 instruction is 16 times faster and does
-// overlap (128 and 144 us apart, 192 together). Both operands are therefore held as exact sums
-// of three bf16 parts, x = h + m + l (24 bits of significand, round to nearest each time), and a
+// overlap (128 and 144 us apart, 192 together). Both operands are therefore held as sums of three
+// bf16 parts, x = h + m + l (24 bits of significand, round to nearest each time; exact from 2^-109
+// on, within 2^-134 below: a coefficient down there keeps fewer bits than fp32 held, and an
+// infinite one becomes NaN), and a
 // product is formed from the parts' products hh, hm, mh, mm, hl, lh (up to lmax 7, where there is
 // room, also ml and lm), accumulated in fp32: what is left out is below 2^-24 of the term.
 //
