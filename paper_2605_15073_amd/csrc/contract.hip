@@ -222,13 +222,13 @@ constexpr int kSB = 34;          // LDS row stride of a staged X row (kCk * kLG 
 constexpr int kSW = kTile + 16;  // LDS row stride of Ws: lane groups of a half-wave apart
 constexpr int kNX = kTile * kCk * kLG / kThreadsC;  // staged elements per thread and slice
 
-// Finite values above bf16's largest, which would round to infinity, as that (the parts that follow
-// hold the rest); NaN stays NaN.
+// Values clamped to bf16's largest, so that a finite first part is left of finite ones (the parts
+// that follow hold the rest, and infinity or NaN).
 __device__ __forceinline__ float2_t saturate(float2_t v)
 {
     constexpr float top = 0x1.fep127f;
 #pragma unroll
-    for (int k = 0; k < 2; ++k) v[k] = v[k] > top ? top : v[k] < -top ? -top : v[k];
+    for (int k = 0; k < 2; ++k) v[k] = __builtin_amdgcn_fmed3f(v[k], -top, top);
     return v;
 }
 
@@ -351,8 +351,8 @@ __global__ __launch_bounds__(kThreadsC, 4) void k_contract_kdeg(
 #pragma unroll
                     for (int q = 0; q < 3; ++q) {
                         const uint2_t w = {
-                            __builtin_bit_cast(unsigned, __builtin_convertvector(saturate(lo), bf2_t)),
-                            __builtin_bit_cast(unsigned, __builtin_convertvector(saturate(hi), bf2_t))};
+                            __builtin_bit_cast(unsigned, __builtin_convertvector(q ? lo : saturate(lo), bf2_t)),
+                            __builtin_bit_cast(unsigned, __builtin_convertvector(q ? hi : saturate(hi), bf2_t))};
                         y[q * ndg * 16 * vw] = w;
                         lo[0] -= __builtin_bit_cast(float, w[0] << 16);
                         lo[1] -= __builtin_bit_cast(float, w[0] & 0xffff0000u);
