@@ -331,15 +331,16 @@ int cgtp_stage_times(cgtp_plan plan, int op, double *ms, int cap, int *n_stages,
 
 /* Measurement helper, not part of the method: the read-pattern ceiling of the message-passing
  * receiver. Replays, for the CSR (row_ptr, col) of cgtp_message_pass, exactly the sender-field
- * loads of the plan's receiver, in its block order, over fields [n_nodes][R][3][UVs]
- * (UVs = n_theta * n_phi rounded up to 32; contents arbitrary), and computes nothing from them;
+ * loads of the plan's receiver, in its block order, over a buffer of n_nodes R 3 UVs floats
+ * (UVs = n_theta * n_phi rounded up to 32; contents arbitrary; the receivers lay the senders'
+ * values out in it in their own ways), and computes nothing from them;
  * sink is a device float written at most once. Its time is the floor the receiver's gather
  * pattern sets on the memory path. The receivers take the surface curl with both derivatives
- * moved onto the analysis (integration by parts on the sphere), so they read only the value
- * plane (plane 0) of each sender rank, once per edge: 4 R n_theta n_phi bytes per edge.
- * Supported for fp32 plans whose receiver is the MFMA one on the plain sender layout (the
- * default grid below lmax 7, R a multiple of 16) or the per-thread one (grids of at most 1024
- * points). Asynchronous on stream.
+ * moved onto the analysis (integration by parts on the sphere), so they read only the
+ * values of each sender rank, once per edge: 4 R n_theta n_phi bytes per edge (R rounded up to 16
+ * on the MFMA receiver). Supported for fp32 plans on the default grid with more than 8 ranks,
+ * below lmax 7 or, if R is no multiple of 16, up to 1024 points, and for those whose receiver is
+ * the per-thread one, up to 1024 points. Asynchronous on stream.
  * Errors: CGTP_ERR_ARG (NULL, sizes, fields_bytes too small), CGTP_ERR_UNSUPPORTED (another
  * receiver), CGTP_ERR_HIP. */
 int cgtp_gather_probe(cgtp_plan plan, int64_t n_nodes, int64_t n_edges, const int32_t *row_ptr,

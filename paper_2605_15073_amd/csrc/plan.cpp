@@ -78,12 +78,12 @@ struct Layout {
 
 // Message passing in the values-only form (the moved-derivative curl: only the senders' values
 // are read, with per-block factors (split) the Gaunt and the curl factors'): fp32, zonal edge
-// field, the default grid (for the MFMA analysis of its moved planes), more than 8 ranks (fewer
-// would fill less than a quarter of the receiver's two rank tiles; the per-thread receiver takes
-// them eight at a time); every lmax.
-bool mfma_values_only(const cgtp_plan_s *p, int R, bool split)
+// field, the default grid (for the MFMA analysis of its moved planes), every lmax, and more than 8
+// ranks: the per-thread receiver takes 8 at a time, and 9 to 12 on it were slower than 16 on this
+// one at every degree measured (9 ranks, 27 edges a node: 4,000 nodes, lmax 1 0.84 of its time;
+// 1,000 nodes, lmax 6 0.65; 250 nodes, lmax 20 0.35).
+bool mfma_values_only(const cgtp_plan_s *p, int R)
 {
-    (void)split;
     return p->dtype == CGTP_F32 && !(p->flags & CGTP_EDGE_SEPARATED) && R > 8 &&
            cgtp::sender_mfma_supported(p->d);
 }
@@ -93,13 +93,13 @@ bool mfma_values_only(const cgtp_plan_s *p, int R, bool split)
 // do not mix before the projection.
 int mp_rank(const cgtp_plan_s *p, int R, bool split)
 {
-    return mfma_values_only(p, R, split) ? (R + 15) / 16 * 16 : R;
+    return mfma_values_only(p, R) ? (R + 15) / 16 * 16 : R;
 }
 
 // Whether the edge coefficients of that form are bf16 parts (else floats).
 bool mp_edge_parts(const cgtp_plan_s *p, int R, bool split)
 {
-    return mfma_values_only(p, R, split) &&
+    return mfma_values_only(p, R) &&
            !cgtp::receiver_values_f32(p->d.lmax, mp_rank(p, R, split), split);
 }
 
@@ -108,7 +108,7 @@ bool mp_edge_parts(const cgtp_plan_s *p, int R, bool split)
 // the SIMT receiver compute-bound.
 bool use_mfma_receiver(const cgtp_plan_s *p, int R, bool split = false)
 {
-    return mfma_values_only(p, R, split) ||
+    return mfma_values_only(p, R) ||
            (p->dtype == CGTP_F32 && !(p->flags & CGTP_EDGE_SEPARATED) &&
             p->d.lmax >= cgtp::kMfmaRecvMinL && cgtp::receiver_mfma_supported(p->d, R));
 }
@@ -119,7 +119,7 @@ bool use_mfma_receiver(const cgtp_plan_s *p, int R, bool split = false)
 bool values_only_form(const cgtp_plan_s *p, int R, bool split)
 {
     if (p->flags & CGTP_EDGE_SEPARATED) return false;
-    return !use_mfma_receiver(p, R, split) || mfma_values_only(p, R, split);
+    return !use_mfma_receiver(p, R, split) || mfma_values_only(p, R);
 }
 
 // On-site workspace: HA, HB, Ta, Tb, each [N][R][K] (R: the plan's rank, or the total
@@ -153,13 +153,14 @@ bool zonal_mfma_analysis(const cgtp_plan_s *p, int R, bool split)
            !use_mfma_receiver(p, R, split) && cgtp::sender_mfma_supported(p->d);
 }
 
-// Message-passing workspace: HI [N][R][K], SF [N][R][3][UVs], Rt [E][L][R], Ta, Tb [N][R][K],
-// and the summed grid fields S: [N][R][2][UVs] for the MFMA receiver, [N][R][3 or 6][UVs] for
-// the zonal one handing over to the MFMA analysis. With two node slots,
-// HI and SF hold the natural slot followed by the flipped one. With split factors (general
-// path), HI and Rt hold the Gaunt factors' contraction followed by the curl factors'. Last,
-// room for one sector's output weights concatenated over the groups (the general path's
-// gathered projection).
+// Message-passing workspace: HI [N][R][K], SF, Rt, Ta, Tb [N][R][K] and the summed grid fields S:
+// [N][R][2][UVs] for the MFMA receiver on three planes, [N][R][3 or 6][UVs] for the values-only
+// form and for the zonal receiver handing over to the MFMA analysis. SF is [N][R][3][UVs] and Rt
+// [E][L][R], but in the values-only form, whose R is mp_rank's: SF the value field in tiles, one
+// plane (two with split factors), Rt as rt_bytes. With two node slots, HI and SF hold the natural
+// slot followed by the flipped one. With split factors (general path), HI and Rt hold the Gaunt
+// factors' contraction followed by the curl factors'. Last, room for one sector's output weights
+// concatenated over the groups (the general path's gathered projection).
 Layout mp_layout(const cgtp_plan_s *p, int R, int64_t N, int64_t E, bool two = false,
                  bool split = false)
 {
@@ -169,9 +170,9 @@ Layout mp_layout(const cgtp_plan_s *p, int R, int64_t N, int64_t E, bool two = f
     R = mp_rank(p, R, split);
     size_t h = align256(es * (size_t)N * R * p->d.K);
     // values only: one plane of tiles (two with split factors); otherwise three fields
-    const size_t sf_planes = mfma_values_only(p, R, split) ? (split ? 2 : 1) : 3;
+    const size_t sf_planes = mfma_values_only(p, R) ? (split ? 2 : 1) : 3;
     size_t sf = align256(es * (size_t)N * R * sf_planes * p->d.UVs);
-    size_t rt = align256(mfma_values_only(p, R, split) ? cgtp::rt_bytes(p->d.lmax, E, R, split)
+    size_t rt = align256(mfma_values_only(p, R) ? cgtp::rt_bytes(p->d.lmax, E, R, split)
                                                        : es * (size_t)E * R * p->d.L);
     const int sg_planes = values_only_form(p, R, split) ? (two ? 6 : 3) : 2;
     size_t sg = use_mfma_receiver(p, R, split)
@@ -482,7 +483,7 @@ int run_mp(cgtp_plan_s *p, int op, int64_t N, int64_t E, const int32_t *row_ptr,
         T *h = slot ? HIf : HI, *sf = slot ? SFf : SF;
         const int planes = values_only ? 1 : 7;
         if constexpr (sizeof(T) == 4) {
-            if (mfma_values_only(p, R, false))
+            if (mfma_values_only(p, R))
                 e = cgtp::launch_sender_mfma(tb, N, Rp, h, sf, true, s);
             else
                 e = cgtp::launch_sender_fields<T>(tb, N, Rp, h, sf, s, planes);
@@ -820,7 +821,7 @@ int run_mp_groups(cgtp_plan_s *p, const Groups &G, int64_t N, int64_t E, const i
         const int planes =
             G.split ? (pass ? (values_only ? 8 : 6) : 1) : (values_only ? 1 : 7);
         if constexpr (sizeof(T) == 4) {
-            if (mfma_values_only(p, Rs, G.split))
+            if (mfma_values_only(p, Rs))
                 e = cgtp::launch_sender_mfma(tb, N, Rg, h,
                                              SF + (pass ? (int64_t)N * Rg * d.UVs : 0), true, s);
             else
@@ -1541,11 +1542,11 @@ int cgtp_gather_probe(cgtp_plan plan, int64_t n_nodes, int64_t n_edges, const in
     if (!plan) return fail(CGTP_ERR_ARG, "plan is NULL");
     if (n_nodes < 0 || n_edges < 0 || n_edges >= 0x7fffffffLL)
         return fail(CGTP_ERR_ARG, "bad sizes");
-    // the receiver of cgtp_message_pass on this plan: the MFMA one in its values-only form (the
-    // probe covers its lower degrees, and ranks that are no multiple of 16 on grids of at most
-    // 1024 points), or the per-thread zonal one
+    // the receiver of cgtp_message_pass on this plan: the MFMA one in its values-only form, or the
+    // per-thread zonal one. The plans taken are those that were taken before the former read
+    // tiles: below lmax 7, and ranks that are no multiple of 16 on grids of at most 1024 points
     const bool mfma = use_mfma_receiver(plan, plan->R);
-    const bool mfma_plain = mfma && mfma_values_only(plan, plan->R, false) &&
+    const bool mfma_plain = mfma && mfma_values_only(plan, plan->R) &&
                             (plan->d.lmax < cgtp::kMfmaRecvMinL ||
                              (plan->R % 16 != 0 && plan->d.UV <= 1024));
     if (plan->dtype != CGTP_F32 || (plan->flags & CGTP_EDGE_SEPARATED) || (mfma && !mfma_plain) ||

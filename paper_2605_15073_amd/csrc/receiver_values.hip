@@ -37,8 +37,8 @@
 // them: SF [N][R/16][UVs/16][64 lanes][4], lane 16 g + n holding ranks 4 g .. 4 g + 3 of point
 // n (with per-block factors a second such plane follows). One 16-byte load per lane then
 // fetches whole lines; the same bytes as rows [R][UVs], 16 segments of 64 bytes per load, ran
-// at a third of the rate (the loads alone, 10^4 nodes, lmax 6, R = 128, 525,308 edges: 5.56 ms
-// in rows, 1.8 ms in tiles; lmax 20, 5,000 nodes, R = 64: 13.7 and 4.4 ms).
+// at two thirds of the rate (the loads alone, 10^4 nodes, lmax 6, R = 128, 525,308 edges, Hilbert
+// order: 5.4 to 5.6 ms in rows, 3.5 to 3.7 ms in tiles).
 //
 // A wave owns RT rank tiles x PT point tiles of one receiver and works alone. P_l and P_l' of an
 // edge do not depend on the rank: a lane runs the recurrence at one point for one of 4 / PT
@@ -52,8 +52,9 @@
 // points): 10^4 nodes, lmax 6, R = 128, 525,308 edges 6.98 -> 5.58 ms; 5,000 nodes, lmax 20,
 // R = 64, 35.0 -> 27.9 ms; two slots, 5,000 nodes, lmax 6, R = 128, 6.81 -> 4.56 ms; per-block
 // factors, 3,000 nodes, lmax 6, 128 stacked ranks, 3.78 -> 3.06 ms. What bounds it now is the
-// power limit: it needs a third fewer cycles than the fp32 form, but the clock falls from 2.05
-// to 1.75 GHz with matrix cores (31% busy), vector ALU (56%) and gather all running.
+// power limit: it needs a third fewer cycles than the fp32 form, but with matrix cores (32% busy),
+// vector ALU (50%) and gather all running the clock falls to 1.76 to 1.87 GHz (2.2 in the
+// contractions, 2.4 in the gather alone). The per-block factors are on the fp32 form by now.
 #include <type_traits>
 
 #include "internal.h"
