@@ -1,7 +1,7 @@
 """The folded on-site kernels against the fp64 oracle over their degrees: every register and LDS
-shape (lmax 0 to 20; 21 takes the matrix-core kernel, and so do few rows from 15), rank blocks with remainders, and grids off
-the default one, whose Gauss-Legendre rows are not held in registers. fp32 bar of the other parity
-tests (2e-5 of the largest output)."""
+shape (lmax 0 to 20; 21 takes the matrix-core kernel, and so do few rows from 15), rank blocks with
+remainders, and grids off the default one, whose Gauss-Legendre rows are not held in registers. fp32
+bar of the other parity tests (2e-5 of the largest output)."""
 from __future__ import annotations
 
 import numpy as np
@@ -41,8 +41,7 @@ def test_folded_onsite(cg, lmax, R, grid):
 
 @pytest.mark.parametrize("lmax,n,R", [(15, 64, 8), (15, 57, 9), (16, 96, 16), (16, 140, 11),
                                       (17, 64, 16), (17, 70, 15), (18, 41, 25), (19, 60, 18),
-                                      (20, 1, 1), (20, 128, 8),
-                                      (20, 79, 13)])
+                                      (20, 1, 1), (20, 128, 8), (20, 79, 13)])
 def test_onsite_rows(cg, lmax, n, R):
     """Degrees that the matrix-core kernel serves for few (node, rank) rows and the folded one for
     more: the last row count of the one and the first of the other."""
